@@ -23,7 +23,7 @@ struct BandArgs {
     uint32_t* err;      // set when a wait for a neighbour gives up
     uint32_t general;   // 1: the (s, m) classes (h != 0), 0: the two h = 0 classes
     BitsLattice bl;
-    AcceptTable at;     // the acceptance table (byte-resident bands)
+    AcceptTable at;     // the acceptance table (a wave per row)
 };
 
 // A wave sweeps a band row in chunks of 64 words (a word per lane); rows of
@@ -37,10 +37,24 @@ inline uint32_t band_lds_bytes(uint32_t L, uint32_t G, uint32_t Wr) { return 2u 
 // Workgroups of `threads` threads that can be resident at once for bands of
 // lds_bytes each and rows of Wr words (0 on error).
 uint32_t bands_capacity(uint32_t threads, uint32_t lds_bytes, bool general, uint32_t Wr);
-// One cooperative launch of G band workgroups of `threads` threads. Sides
-// 512, 1024 and 2048, and 4096 with h != 0, keep their bands as bytes when
-// those fit (the fused kernels' word update), every other side as bits.
-hipError_t launch_bands(const BandArgs& a, uint32_t G, uint32_t threads, hipStream_t s);
+// Bands of a wave per row (ising_band_rows.hip): words a lane, how rows end
+// (kRows*), half-sweeps between exchanges, threads and LDS of a workgroup.
+struct RowBandShape {
+    uint32_t cw, mode, depth, threads, lds;
+};
+// The shape for G bands of side L (any even side); false if a row does not
+// fit a wave or a band with its outside rows does not fit a workgroup.
+bool row_band_shape(uint32_t L, uint32_t G, RowBandShape* out);
+const void* row_band_kernel(const RowBandShape& s);
+// Tagged words its edge slots and load flags take (0 if not served).
+size_t row_band_pub_words(uint32_t L, uint32_t G);
+// Whether G bands of side L run with a wave per row on the current device.
+bool row_bands_serve(uint32_t L, uint32_t G);
+
+// One cooperative launch of G band workgroups, a wave per row where
+// `row_waves` and row_bands_serve allow it, else bits with `threads` threads
+// (L % 8 == 0 only).
+hipError_t launch_bands(const BandArgs& a, uint32_t G, uint32_t threads, bool row_waves, hipStream_t s);
 // Zero `words` tagged edge words (before tags restart from 0).
 hipError_t launch_bands_clear(uint64_t* pub, size_t words, hipStream_t s);
 // Sum each sweep's G band partials into ser (2 int64 per sweep, n sweeps).

@@ -82,12 +82,8 @@ constexpr uint32_t kFusedMinTiles = 16384;
 // by more than this fraction (timing noise must not flip the choice).
 constexpr float kTuneMargin = 0.03f;
 // Band plan: sides it serves by default, and sweeps per launch (the
-// partials of a launch are bands x sweeps pairs). Its default band height
-// gives about one band per compute unit: one band a CU measured fastest
-// from 192 to 16384 (fewer bands leave CUs idle, more put unequal numbers of
-// bands on CUs; at the small sides a band's half-sweep is bound by the
-// latency of its rows and of the edge exchange, not by the chip's rate).
-constexpr uint32_t kBandMinDefaultL = 192;
+// partials of a launch are bands x sweeps pairs).
+constexpr uint32_t kBandMinDefaultL = 136;
 constexpr uint32_t kBandChunk = ISING_BAND_SWEEPS_PER_LAUNCH;
 constexpr uint32_t kTuneRounds = 3;
 
@@ -174,6 +170,12 @@ static bool bands_fit(uint32_t L, uint32_t rows, uint32_t per_wave) {
     return cap >= G;
 }
 
+// Default band height: about one band per compute unit, but at least four
+// rows (a band of four trades its edges every four half-sweeps, one of two
+// every two: 256^2 1.60 us a sweep with four rows, 1.95 with two, 2.56 with
+// one; 512^2 1.57 and 1.98), and 16 rows rather than 12 to 15 (no rows
+// outside the band to update: 3072^2 5.6 us with 16, 5.9 with 12; eight to
+// eleven rows measure the same as 16 or better).
 static uint32_t band_default_rows(uint32_t L) {
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
@@ -181,7 +183,8 @@ static uint32_t band_default_rows(uint32_t L) {
         (void)hipGetLastError();
         cus = 256;
     }
-    return std::max<uint32_t>(1u, (L + (uint32_t)cus - 1u) / (uint32_t)cus);
+    const uint32_t rows = std::max<uint32_t>(4u, (L + (uint32_t)cus - 1u) / (uint32_t)cus);
+    return std::min<uint32_t>(rows > 11u && rows < 16u ? 16u : rows, std::max<uint32_t>(1u, L / 2u));
 }
 
 bool plan_for(uint32_t L, uint32_t kind, uint32_t cw, uint32_t rows, Plan* out) {
@@ -324,15 +327,21 @@ int ctx_reserve_series(ising_ctx* ctx, uint64_t more) {
     return ISING_OK;
 }
 
+// Tagged edge-row words for G bands of side L, whichever kernel runs them.
+static size_t band_slot_words(uint32_t L, uint32_t G) {
+    const size_t bits = L % 8u == 0u ? band_pub_words(G, band_words(L)) : 0;
+    return std::max(bits, row_band_pub_words(L, G));
+}
+
 // The band plan's edge-row slots for G bands and its timeout mark (the
 // slots only grow; growing waits for the launches that may still use them).
 static int ctx_band_slots(ising_ctx* ctx, uint32_t G) {
-    if (G > ctx->band_cap) {
-        if (ctx->band_cap) HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+    const size_t words = band_slot_words(ctx->L, G);
+    if (words > ctx->band_words) {
+        if (ctx->band_words) HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
         if (ctx->band_pub) (void)hipFree(ctx->band_pub);
         ctx->band_pub = nullptr;
-        ctx->band_cap = 0;
-        const size_t words = band_pub_words(G, band_words(ctx->L));
+        ctx->band_words = 0;
         if (hipMalloc(&ctx->band_pub, words * sizeof(uint64_t)) != hipSuccess) {
             (void)hipGetLastError();
             return ISING_ENOMEM;
@@ -340,18 +349,63 @@ static int ctx_band_slots(ising_ctx* ctx, uint32_t G) {
         // fresh slots carry tag 0, below every tag a launch waits for
         HIP_TRY(ctx, hipMemsetAsync(ctx->band_pub, 0, words * sizeof(uint64_t), ctx->stream));
         ctx->band_base = 0;
-        ctx->band_cap = G;
+        ctx->band_words = words;
     }
-    if (!ctx->band_err) {
-        if (hipMalloc(&ctx->band_err, sizeof(uint32_t)) != hipSuccess ||
-            hipHostMalloc(&ctx->band_err_host, sizeof(uint32_t), hipHostMallocDefault) != hipSuccess) {
+    if (!ctx->band_err_host) {
+        if (hipHostMalloc(&ctx->band_err_host, sizeof(uint32_t), hipHostMallocDefault) != hipSuccess) {
             (void)hipGetLastError();
             return ISING_ENOMEM;
         }
         *ctx->band_err_host = 0;
-        HIP_TRY(ctx, hipMemsetAsync(ctx->band_err, 0, sizeof(uint32_t), ctx->stream));
+        void* dev = nullptr;
+        HIP_TRY(ctx, hipHostGetDevicePointer(&dev, ctx->band_err_host, 0));
+        ctx->band_err = static_cast<uint32_t*>(dev);
     }
     return ISING_OK;
+}
+
+// The band plan's partials for launches of kBandChunk sweeps (G pairs a
+// sweep), allocated on the first ising_sweep of a band plan (a context that
+// only runs in batches never needs them, and ising_sweep_static uses the
+// library's array instead).
+static int ctx_band_part(ising_ctx* ctx, uint32_t G) {
+    if (ctx->band_part && ctx->band_part_cap >= G) return ISING_OK;
+    if (ctx->band_part) {
+        HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+        (void)hipFree(ctx->band_part);
+        ctx->band_part = nullptr;
+        ctx->band_part_cap = 0;
+    }
+    if (hipMalloc(&ctx->band_part, (size_t)kBandChunk * G * 2 * sizeof(int64_t)) != hipSuccess) {
+        (void)hipGetLastError();
+        ctx->band_part = nullptr;
+        return ISING_ENOMEM;
+    }
+    ctx->band_part_cap = G;
+    return ISING_OK;
+}
+
+// Bands of a per-site (ISING_PLAN_GENERIC) context whose side is not a
+// multiple of 8: its sweeps run band-resident, a wave per row, where the
+// rows fit (0: they do not, or the plan was forced on a side of whole
+// words). A per-site sweep is three launches, one of them a whole pass for
+// the observables: 57.4 us at 1002^2 against 2.5 us.
+static uint32_t generic_bands(const ising_ctx* ctx) {
+    if (ctx->plan.kind != ISING_PLAN_GENERIC || ctx->L % 8u == 0u) return 0;
+    const uint32_t G = band_count(ctx->L, band_default_rows(ctx->L));
+    return row_bands_serve(ctx->L, G) ? G : 0;
+}
+
+// Whether a call of n sweeps on a resident-plan context of a side the plan
+// is the default for runs on bands instead. One workgroup sweeps in about
+// 0.67 + 1.8e-4 L^2 us, bands of four rows in 1.5 us at any of these sides,
+// but a band call costs about 12 us more around its sweeps (a cooperative
+// launch, the sum of its partials): at 128 the bands win from 7 sweeps up
+// (398.7 against 191.3 us for 100), at 96 from 15, at 72 from 60, at 64 never.
+static bool resident_on_bands(const ising_ctx* ctx, uint64_t n) {
+    const uint64_t sites = (uint64_t)ctx->L * ctx->L;
+    return ctx->L <= kResidentMaxL && sites > 4400u && n * (sites - 4400u) >= 100000u &&
+           row_bands_serve(ctx->L, band_count(ctx->L, band_default_rows(ctx->L)));
 }
 
 // Allocate what the context's plan needs: the second lattice buffer for
@@ -368,6 +422,11 @@ int ctx_prepare_plan(ising_ctx* ctx) {
     }
     if (ctx->plan.kind == ISING_PLAN_BANDS) {
         const int rc = ctx_band_slots(ctx, band_count(ctx->L, ctx->plan.rows));
+        if (rc != ISING_OK) return rc;
+    }
+    if (const uint32_t G = generic_bands(ctx)) {
+        int rc = ctx_band_slots(ctx, G);
+        if (rc == ISING_OK) rc = ctx_band_part(ctx, G);  // here: ising_sweep_static may not allocate
         if (rc != ISING_OK) return rc;
     }
     uint32_t need = 0;
@@ -425,26 +484,6 @@ static int sweep_fused(ising_ctx* ctx, uint64_t n, int64_t* ser, int64_t* part0,
     return ISING_OK;
 }
 
-// The band plan's partials for launches of kBandChunk sweeps, allocated on
-// the first ising_sweep (a context that only runs in batches never needs
-// them, and ising_sweep_static uses the library's array instead).
-static int ctx_band_part(ising_ctx* ctx, uint32_t G) {
-    if (ctx->band_part && ctx->band_part_cap >= G) return ISING_OK;
-    if (ctx->band_part) {
-        HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-        (void)hipFree(ctx->band_part);
-        ctx->band_part = nullptr;
-        ctx->band_part_cap = 0;
-    }
-    if (hipMalloc(&ctx->band_part, (size_t)kBandChunk * G * 2 * sizeof(int64_t)) != hipSuccess) {
-        (void)hipGetLastError();
-        ctx->band_part = nullptr;
-        return ISING_ENOMEM;
-    }
-    ctx->band_part_cap = G;
-    return ISING_OK;
-}
-
 // n sweeps of the band plan with bands of `rows` rows, `per_wave` rows a
 // wave: launches of up to `chunk` sweeps, each followed by the sum of its
 // bands' partials (at part) into ser.
@@ -471,19 +510,32 @@ static int sweep_bands(ising_ctx* ctx, uint64_t n, int64_t* ser, int64_t* part, 
         const uint32_t m = (uint32_t)std::min<uint64_t>(n - done, chunk);
         if ((uint64_t)ctx->band_base + 2ull * m >= 0xffffffffull) {
             // the tags would wrap: clear every slot and count from 0 again
-            HIP_TRY(ctx, launch_bands_clear(ctx->band_pub, band_pub_words(ctx->band_cap, a.Wr), ctx->stream));
+            HIP_TRY(ctx, launch_bands_clear(ctx->band_pub, ctx->band_words, ctx->stream));
             ctx->band_base = 0;
         }
         a.t0 = (uint32_t)(ctx->t + done);
         a.n = m;
         a.base = ctx->band_base;
-        HIP_TRY(ctx, launch_bands(a, G, band_threads(L, G, per_wave), ctx->stream));
+        HIP_TRY(ctx, launch_bands(a, G, band_threads(L, G, per_wave), per_wave == 1u, ctx->stream));
         // every slot the launch used ends it tagged base + 2 m or base + 2 m - 1
         ctx->band_base += 2u * m;
         HIP_TRY(ctx, launch_bands_reduce(part, G, m, ser + 2 * done, ctx->stream));
         done += m;
     }
     return ISING_OK;
+}
+
+// Whether work enqueued on s is being captured into a graph. The band plan
+// must not be captured: each launch's edge-row tags start from a base the
+// host advances per launch, so a replayed launch would find the slots
+// still holding the previous replay's words under the tags it waits for.
+static bool stream_capturing(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return st != hipStreamCaptureStatusNone;
 }
 
 // n sweeps of the two-pass plan; per-block partials in part (nb pairs).
@@ -587,6 +639,13 @@ static int sweep_replays(ising_ctx* ctx, uint64_t n, uint64_t* left) {
 }
 
 static int sweep_generic(ising_ctx* ctx, uint64_t n, int64_t* ser) {
+    // not under capture: a band launch's tags advance on the host. One sweep
+    // of a small lattice is faster as its three per-site launches (37 against
+    // 44 us for the call at 66^2; from two sweeps the bands win, 46 against 70).
+    const bool direct = (n == 1 && ctx->L <= 256u) || stream_capturing(ctx->stream);
+    const uint32_t G = direct ? 0 : generic_bands(ctx);
+    if (G && ctx->band_part_cap >= G)
+        return sweep_bands(ctx, n, ser, ctx->band_part, kBandChunk, band_default_rows(ctx->L), 1u);
     const uint32_t k0 = (uint32_t)ctx->p.seed, k1 = (uint32_t)(ctx->p.seed >> 32);
     HIP_TRY(ctx, launch_zero(ser, 2 * n, ctx->stream));
     const Planes pl = ctx_planes(ctx);
@@ -720,19 +779,6 @@ int ising_reserve(ising_ctx* ctx, uint64_t sweeps) {
     return ctx_reserve_series(ctx, sweeps);
 }
 
-// Whether work enqueued on s is being captured into a graph. The band plan
-// must not be captured: each launch's edge-row tags start from a base the
-// host advances per launch, so a replayed launch would find the slots
-// still holding the previous replay's words under the tags it waits for.
-static bool stream_capturing(hipStream_t s) {
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    return st != hipStreamCaptureStatusNone;
-}
-
 int ising_sweep(ising_ctx* ctx, uint64_t n) {
     int rc = ctx_enter(ctx);
     if (rc != ISING_OK) return rc;
@@ -742,6 +788,18 @@ int ising_sweep(ising_ctx* ctx, uint64_t n) {
     rc = ctx_reserve_series(ctx, n);
     if (rc != ISING_OK) return rc;
     ++ctx->gen;
+    if (ctx->plan.kind == ISING_PLAN_RESIDENT && resident_on_bands(ctx, n) && !stream_capturing(ctx->stream)) {
+        const uint32_t rows = band_default_rows(ctx->L), G = band_count(ctx->L, rows);
+        rc = ctx_band_slots(ctx, G);
+        if (rc == ISING_OK) rc = ctx_band_part(ctx, G);
+        if (rc == ISING_OK)
+            rc = sweep_bands(ctx, n, ctx->series + 2 * ctx->series_len, ctx->band_part, kBandChunk, rows, 1u);
+        if (rc == ISING_OK) {
+            ctx->t += n;
+            ctx->series_len += n;
+        }
+        if (rc != ISING_ENOMEM) return rc;  // no room for the bands' buffers: one workgroup does it
+    }
     if (ctx->plan.kind == ISING_PLAN_RESIDENT) {
         // one workgroup runs every sweep from local memory (bytes: a lone
         // lattice's latency, not the chip's throughput, sets the time)
@@ -763,7 +821,13 @@ int ising_sweep(ising_ctx* ctx, uint64_t n) {
         case ISING_PLAN_GENERIC: rc = sweep_generic(ctx, n, ser); break;
         case ISING_PLAN_BANDS:
             rc = ctx_band_part(ctx, band_count(ctx->L, ctx->plan.rows));
-            if (rc == ISING_OK) rc = sweep_bands(ctx, n, ser, ctx->band_part, kBandChunk, ctx->plan.rows, ctx->plan.cw);
+            // one or two sweeps of a side below 192: a launch per colour costs
+            // less than a cooperative launch (136: 35 and 42 us a call against
+            // 44 and 45; three sweeps and more, or 192 and up, bands)
+            if (rc == ISING_OK && n <= 2 && ctx->L < 192u &&
+                two_pass_blocks(ctx_planes(ctx), 1) <= kBandChunk * ctx->band_part_cap)
+                rc = sweep_two_pass(ctx, n, ser, ctx->band_part, 1);
+            else if (rc == ISING_OK) rc = sweep_bands(ctx, n, ser, ctx->band_part, kBandChunk, ctx->plan.rows, ctx->plan.cw);
             break;
         default: return ISING_EUNSUPPORTED;
     }
@@ -949,16 +1013,11 @@ static int ensure_canonical(ising_ctx* ctx) {
 
 // The band plan's edge waits give up only when a neighbouring band stopped
 // publishing (the bands were not all resident): the launch's results are
-// then not valid. Copy its mark back with a read-back, check it after.
-static int enqueue_band_check(ising_ctx* ctx) {
-    if (ctx->band_err)
-        HIP_TRY(ctx, hipMemcpyAsync(ctx->band_err_host, ctx->band_err, sizeof(uint32_t), hipMemcpyDeviceToHost,
-                                    ctx->stream));
-    return ISING_OK;
-}
-
+// then not valid. The launch marks a word in pinned host memory, read here
+// once the stream is synchronised (copying a device word back with every
+// read-back took 7 us of a short call).
 static int band_check(ising_ctx* ctx) {
-    if (ctx->band_err_host && *ctx->band_err_host)
+    if (ctx->band_err_host && *(volatile const uint32_t*)ctx->band_err_host)
         return ctx_fail(ctx, hipErrorLaunchTimeOut, "band plan: a wait for a neighbouring band gave up");
     return ISING_OK;
 }
@@ -972,8 +1031,6 @@ int ising_copy_spins(ising_ctx* ctx, int8_t* host, size_t n) {
     if (rc != ISING_OK) return rc;
     HIP_TRY(ctx, launch_to_canonical(ctx_planes(ctx), ctx->canon, ctx->stream));
     HIP_TRY(ctx, hipMemcpyAsync(host, ctx->canon, N, hipMemcpyDeviceToHost, ctx->stream));
-    rc = enqueue_band_check(ctx);
-    if (rc != ISING_OK) return rc;
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     return band_check(ctx);
 }
@@ -1046,7 +1103,7 @@ static int enqueue_readback(ising_ctx* ctx, uint32_t want, bool full, int64_t* s
         HIP_TRY(ctx, launch_to_canonical(ctx_planes(ctx), ctx->canon, ctx->stream));
         HIP_TRY(ctx, hipMemcpyAsync(bytes, ctx->canon, N, hipMemcpyDeviceToHost, ctx->stream));
     }
-    return enqueue_band_check(ctx);
+    return ISING_OK;
 }
 
 int ising_prefetch_observables(ising_ctx* ctx, uint32_t want) {
@@ -1491,7 +1548,6 @@ int ising_destroy(ising_ctx* ctx) {
     if (ctx->cpart) (void)hipFree(ctx->cpart);
     if (ctx->band_pub) (void)hipFree(ctx->band_pub);
     if (ctx->band_part) (void)hipFree(ctx->band_part);
-    if (ctx->band_err) (void)hipFree(ctx->band_err);
     if (ctx->band_err_host) (void)hipHostFree(ctx->band_err_host);
     for (int k = 0; k < 2; ++k)
         if (ctx->cfpart[k]) (void)hipFree(ctx->cfpart[k]);
