@@ -50,7 +50,7 @@ typedef struct perc_result {
     /* work measures of the engine (not paper quantities) */
     uint32_t launches;         /* relaxation launches */
     uint32_t pad;
-    uint64_t tile_visits;      /* 64 x 64 tiles relaxed, summed over launches */
+    uint64_t tile_visits;      /* 64 x 64 tiles advanced (by up to 32 passes), summed over launches */
     uint64_t tile_iterations;  /* breadth-first levels run, summed over tile visits */
     uint64_t arrival_hash;  /* FNV-1a-64 of the int32 arrival map, little-endian row-major (opt-in) */
 } perc_result;
@@ -58,15 +58,15 @@ typedef struct perc_result {
 typedef struct perc_ctx perc_ctx; /* opaque, library-owned */
 
 /* Create a context for one medium and allocate its device memory (5 bytes
- * per site plus per-tile work lists) on `stream` (NULL: the library creates
+ * and 3 bits per site plus per-tile flags and work lists) on `stream` (NULL: the library creates
  * and owns one). Errors: EINVAL (invalid params, out == NULL), ENOMEM,
  * EDEVICE. *out is NULL on failure. */
 int perc_create(const perc_params* params, void* stream, perc_ctx** out);
 
 /* Draw the medium and invade it to the steady state. Synchronises (the
  * engine polls its work list between groups of launches). Running again
- * redraws the same medium and gives the same result. Errors: EINVAL,
- * ESTATE, EDEVICE. */
+ * redraws the same medium and gives the same result. The first run also
+ * allocates the work lists. Errors: EINVAL, ESTATE, ENOMEM, EDEVICE. */
 int perc_run(perc_ctx* ctx);
 
 /* Draw and invade the media of `count` contexts together, with the same
@@ -74,7 +74,8 @@ int perc_run(perc_ctx* ctx);
  * tiles of all of them, so many small media fill the GPU (Section 2.3 asks
  * for the porosity from which a spanning cluster exists, a question over
  * many media). Runs on the first context's stream after each context's
- * earlier work. Synchronises. Errors: EINVAL (NULL or repeated contexts,
+ * earlier work; the table and work lists of the batch are kept by the first
+ * context for its next batches and freed with it. Synchronises. Errors: EINVAL (NULL or repeated contexts,
  * contexts on different devices), ESTATE, ERANGE (more than 2^32 tiles
  * together), ENOMEM, EDEVICE (the first context is poisoned). */
 int perc_run_batch(perc_ctx* const* ctxs, size_t count);

@@ -9,11 +9,12 @@ namespace perc {
 
 constexpr uint32_t kTile = 64;               // tile side (sites)
 constexpr uint32_t kThreads = 256;           // per workgroup of the draw, seed and finish passes
-constexpr uint32_t kRelaxThreads = kTile;    // relaxation: one wave per tile, a lane per tile row
-constexpr uint32_t kSolid = 0xffffffffu;     // arrival of a solid site (-1 as int32)
-constexpr uint32_t kUnreached = 0x7fffffffu; // pore not (yet) invaded
+constexpr uint32_t kRelaxThreads = 64;       // relaxation: one wave per tile
+constexpr uint32_t kLevels = 32;             // arrival passes per relaxation launch (half a tile)
+constexpr uint32_t kSubs = 64;               // parts of a work list, each with its own counter
 
-struct Stats {
+// Summary of one medium's run.
+struct Result {
     unsigned long long pores;
     unsigned long long invaded;
     uint32_t max_arrival;
@@ -22,32 +23,53 @@ struct Stats {
     unsigned long long iterations;  // breadth-first levels summed over visits
 };
 
-// One medium of a run (a run relaxes one or several media together).
+struct TileStat {
+    uint32_t visits, iterations, max_arrival, pad;
+};
+
+// One medium of a run (a run relaxes one or several media together). Bit
+// maps are stored tile by tile: 64 rows of 64 bits (bit c: column c).
 struct Medium {
-    uint32_t* arr;        // arrival passes, row-major
+    uint8_t* pore;        // row-major, 1 = pore
+    uint32_t* arr;        // arrival passes, row-major (all ones: solid or not invaded)
+    uint64_t* pmap;       // pores
+    uint64_t* reach[2];   // invaded sites before launch k in reach[k % 2]
     uint32_t* queued[2];  // per tile: is it in work list 0 / 1
-    uint32_t* resume;     // per tile: level from which its next visit must start (all ones: none)
-    Stats* stats;
-    uint32_t L, n_tx, n_ty, pad;
+    TileStat* stat;       // per tile
+    uint64_t pthr;        // a site is a pore iff its draw is below it
+    uint32_t L, n_tx, n_ty;
+    uint32_t k0, k1;      // Philox key
+    uint32_t source, i0, j0;
 };
 
 // Work lists of (medium, tile) entries to relax in a launch. Launch k reads
-// list[k % 2] with length len[k % 3], appends to list[(k + 1) % 2] /
+// list[k % 2] with lengths len[k % 3], appends to list[(k + 1) % 2] /
 // len[(k + 1) % 3] and clears len[(k + 2) % 3]; a medium's queued[p][tile]
-// says whether the tile is in list p, so no tile is listed twice.
+// says whether the tile is in list p, so no tile is listed twice. A list has
+// kSubs parts of `cap` entries: tile (ty, tx) goes to part (tx + 13 ty) %
+// kSubs, so that a front's tiles spread over the parts and their counters.
 struct WorkLists {
     uint2* list[2];
-    uint32_t* len;  // 3 counters
+    uint32_t* len;  // 3 x kSubs counters
+    uint32_t cap;
 };
+__host__ __device__ inline uint32_t list_part(uint32_t tx, uint32_t ty) { return (tx + 13u * ty) % kSubs; }
+// Most entries of a side-L medium that go to one part.
+__host__ __device__ inline uint64_t part_entries(uint32_t L) {
+    const uint64_t n = (L + kTile - 1u) / kTile;
+    return n * ((n + kSubs - 1u) / kSubs);
+}
 
-hipError_t launch_draw(uint8_t* pore, uint32_t* arr, uint32_t L, uint64_t pthr, uint32_t k0, uint32_t k1,
-                       uint32_t source, uint32_t i0, uint32_t j0, Stats* stats, hipStream_t s);
-// clear the list counters (before the media of a run are seeded)
-hipError_t launch_reset_lists(const WorkLists& w, hipStream_t s);
-// append medium m's source tiles to list 0
-hipError_t launch_seed(const WorkLists& w, const Medium* media, uint32_t m, uint32_t n_tx, uint32_t source,
-                       uint32_t i0, uint32_t j0, hipStream_t s);
-hipError_t launch_relax(const Medium* media, const WorkLists& w, uint64_t k, uint32_t grid, hipStream_t s);
-hipError_t launch_finish(uint32_t* arr, uint32_t L, Stats* stats, hipStream_t s);
+// Draw `count` media (max_L the largest side), clear their maps, flags and
+// statistics, the list counters and the results.
+hipError_t launch_draw(const Medium* media, uint32_t count, uint32_t max_L, const WorkLists& w, Result* res,
+                       hipStream_t s);
+// append every medium's source tiles to list 0
+hipError_t launch_seed(const Medium* media, uint32_t count, const WorkLists& w, hipStream_t s);
+// Relaxation launch k over the listed tiles; one: the host's descriptor when
+// the run has a single medium (else nullptr).
+hipError_t launch_relax(const Medium* one, const Medium* media, const WorkLists& w, uint64_t k, uint32_t grid,
+                        hipStream_t s);
+hipError_t launch_finish(const Medium* media, uint32_t count, uint32_t max_L, Result* res, hipStream_t s);
 
 }  // namespace perc
