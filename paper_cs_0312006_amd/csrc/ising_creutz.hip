@@ -115,23 +115,6 @@ __global__ void __launch_bounds__(kCreutzThreads) k_fill_u8(uint8_t* p, uint64_t
     for (uint64_t k = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; k < n; k += stride) p[k] = v;
 }
 
-// Byte planes <-> canonical row-major bytes (demon values copied as is).
-__global__ void __launch_bounds__(kCreutzThreads) k_bytes_to_canonical(Planes pl, uint8_t* out) {
-    const uint64_t N = (uint64_t)pl.L * pl.L, stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t idx = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; idx < N; idx += stride) {
-        const uint32_t i = (uint32_t)(idx / pl.L), j = (uint32_t)(idx - (uint64_t)i * pl.L);
-        out[idx] = pl.p[(i + j) & 1u][(size_t)i * pl.H + (j >> 1)];
-    }
-}
-
-__global__ void __launch_bounds__(kCreutzThreads) k_bytes_from_canonical(Planes pl, const uint8_t* in) {
-    const uint64_t N = (uint64_t)pl.L * pl.L, stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t idx = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; idx < N; idx += stride) {
-        const uint32_t i = (uint32_t)(idx / pl.L), j = (uint32_t)(idx - (uint64_t)i * pl.L);
-        pl.p[(i + j) & 1u][(size_t)i * pl.H + (j >> 1)] = in[idx];
-    }
-}
-
 static uint32_t grid_for(uint64_t n) {
     const uint64_t b = (n + kCreutzThreads - 1) / kCreutzThreads;
     return (uint32_t)(b > 4096 ? 4096 : (b ? b : 1));
@@ -165,16 +148,6 @@ hipError_t launch_demon_sum(const uint8_t* d, uint64_t n, int64_t* out, hipStrea
 
 hipError_t launch_fill_u8(uint8_t* p, uint64_t n, uint8_t v, hipStream_t s) {
     k_fill_u8<<<grid_for(n), kCreutzThreads, 0, s>>>(p, n, v);
-    return hipGetLastError();
-}
-
-hipError_t launch_bytes_to_canonical(const Planes& pl, uint8_t* out, hipStream_t s) {
-    k_bytes_to_canonical<<<grid_for((uint64_t)pl.L * pl.L), kCreutzThreads, 0, s>>>(pl, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_bytes_from_canonical(const Planes& pl, const uint8_t* in, hipStream_t s) {
-    k_bytes_from_canonical<<<grid_for((uint64_t)pl.L * pl.L), kCreutzThreads, 0, s>>>(pl, in);
     return hipGetLastError();
 }
 

@@ -43,8 +43,10 @@ __device__ __forceinline__ void block_add2(int64_t a, int64_t b, int64_t* out) {
 // ---------------------------------------------------------------------------
 // Initial state (Section 2.2): up iff draw(t=0, c, d=1) < pthr.
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) k_init_words(Planes pl, uint32_t c, uint32_t k0, uint32_t k1,
-                                                    uint64_t pthr) {
+// Blocks of y = c draw colour c (one launch: a short run's reset is bound by
+// launches).
+__global__ void __launch_bounds__(256) k_init_words(Planes pl, uint32_t k0, uint32_t k1, uint64_t pthr) {
+    const uint32_t c = blockIdx.y;
     const uint32_t idx = blockIdx.x * blockDim.x + threadIdx.x;
     const uint32_t words = pl.L * pl.Hw;
     if (idx >= words) return;
@@ -58,8 +60,8 @@ __global__ void __launch_bounds__(256) k_init_words(Planes pl, uint32_t c, uint3
 }
 
 // Any even L: one thread per site of colour c, its own Philox call.
-__global__ void __launch_bounds__(256) k_init_sites(Planes pl, uint32_t c, uint32_t k0, uint32_t k1,
-                                                    uint64_t pthr) {
+__global__ void __launch_bounds__(256) k_init_sites(Planes pl, uint32_t k0, uint32_t k1, uint64_t pthr) {
+    const uint32_t c = blockIdx.y;
     const uint32_t idx = blockIdx.x * blockDim.x + threadIdx.x;  // ord = i*H + m
     const uint32_t sites = pl.L * pl.H;
     if (idx >= sites) return;
@@ -270,29 +272,6 @@ __global__ void __launch_bounds__(256) k_observe(Planes pl, int64_t* out) {
     block_add2(b, m, out);
 }
 
-// ---------------------------------------------------------------------------
-// Layout conversion between planes and canonical row-major int8 +1 / -1.
-// ---------------------------------------------------------------------------
-// Grid-stride over the L*L sites (a 65536^2 lattice has 2^32 sites, more
-// than one launch can give a thread each).
-__global__ void __launch_bounds__(256) k_to_canonical(Planes pl, int8_t* out) {
-    const size_t N = (size_t)pl.L * pl.L, stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < N; idx += stride) {
-        const uint32_t i = (uint32_t)(idx / pl.L), j = (uint32_t)(idx - (size_t)i * pl.L);
-        const uint32_t c = (i + j) & 1u;
-        out[idx] = pl.p[c][(size_t)i * pl.H + (j >> 1)] ? (int8_t)1 : (int8_t)-1;
-    }
-}
-
-__global__ void __launch_bounds__(256) k_from_canonical(Planes pl, const int8_t* in) {
-    const size_t N = (size_t)pl.L * pl.L, stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < N; idx += stride) {
-        const uint32_t i = (uint32_t)(idx / pl.L), j = (uint32_t)(idx - (size_t)i * pl.L);
-        const uint32_t c = (i + j) & 1u;
-        pl.p[c][(size_t)i * pl.H + (j >> 1)] = in[idx] > 0 ? 1u : 0u;
-    }
-}
-
 // Fill n int64 with zero (a kernel, not a memset, so it can sit in a graph).
 __global__ void __launch_bounds__(256) k_zero_i64(int64_t* p, uint64_t n) {
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
@@ -306,13 +285,10 @@ static inline uint32_t blocks_for(uint64_t n, uint32_t bs) { return (uint32_t)((
 
 hipError_t launch_init(const Planes& pl, bool words, uint32_t k0, uint32_t k1, uint64_t pthr,
                        hipStream_t s) {
-    for (uint32_t c = 0; c < 2; ++c) {
-        if (words) {
-            k_init_words<<<blocks_for((uint64_t)pl.L * pl.Hw, 256), 256, 0, s>>>(pl, c, k0, k1, pthr);
-        } else {
-            k_init_sites<<<blocks_for((uint64_t)pl.L * pl.H, 256), 256, 0, s>>>(pl, c, k0, k1, pthr);
-        }
-    }
+    if (words)
+        k_init_words<<<dim3(blocks_for((uint64_t)pl.L * pl.Hw, 256), 2), 256, 0, s>>>(pl, k0, k1, pthr);
+    else
+        k_init_sites<<<dim3(blocks_for((uint64_t)pl.L * pl.H, 256), 2), 256, 0, s>>>(pl, k0, k1, pthr);
     return hipGetLastError();
 }
 
@@ -405,18 +381,6 @@ hipError_t launch_zero(int64_t* p, uint64_t n, hipStream_t s) {
     if (n == 0) return hipSuccess;
     const uint32_t nb = blocks_for(n, 256);
     k_zero_i64<<<nb > 4096u ? 4096u : (nb ? nb : 1u), 256, 0, s>>>(p, n);
-    return hipGetLastError();
-}
-
-hipError_t launch_to_canonical(const Planes& pl, int8_t* out, hipStream_t s) {
-    const uint32_t nb = blocks_for((uint64_t)pl.L * pl.L, 256);
-    k_to_canonical<<<nb > 65536u ? 65536u : nb, 256, 0, s>>>(pl, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_from_canonical(const Planes& pl, const int8_t* in, hipStream_t s) {
-    const uint32_t nb = blocks_for((uint64_t)pl.L * pl.L, 256);
-    k_from_canonical<<<nb > 65536u ? 65536u : nb, 256, 0, s>>>(pl, in);
     return hipGetLastError();
 }
 
