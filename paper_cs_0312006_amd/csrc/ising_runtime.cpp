@@ -19,6 +19,7 @@
 #include "ising.h"
 #include "ising_launch.hpp"
 #include "ising_creutz.hpp"
+#include "ising_hostcopy.hpp"
 #include "ising_runtime.hpp"
 
 using namespace ising;
@@ -685,7 +686,9 @@ static int create_common(const ising_params* params, void* dev_buf, size_t bytes
     ctx->L = params->L;
     ctx->plan = plan;
     build_accept_table(params->J, params->h, params->T, &ctx->table, &ctx->exact);
+    hostcopy_retain();
     if (hipGetDevice(&ctx->device) != hipSuccess) {
+        hostcopy_release();
         delete ctx;
         return ISING_EDEVICE;
     }
@@ -693,6 +696,7 @@ static int create_common(const ising_params* params, void* dev_buf, size_t bytes
         ctx->stream = (hipStream_t)stream;
     } else {
         if (hipStreamCreateWithFlags(&ctx->stream, hipStreamNonBlocking) != hipSuccess) {
+            hostcopy_release();
             delete ctx;
             return ISING_EDEVICE;
         }
@@ -1030,8 +1034,7 @@ int ising_copy_spins(ising_ctx* ctx, int8_t* host, size_t n) {
     rc = ensure_canonical(ctx);
     if (rc != ISING_OK) return rc;
     HIP_TRY(ctx, launch_to_canonical(ctx_planes(ctx), ctx->canon, ctx->stream));
-    HIP_TRY(ctx, hipMemcpyAsync(host, ctx->canon, N, hipMemcpyDeviceToHost, ctx->stream));
-    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+    HIP_TRY(ctx, copy_to_host(host, ctx->canon, N, ctx->stream));
     return band_check(ctx);
 }
 
@@ -1526,8 +1529,7 @@ int ising_copy_demons(ising_ctx* ctx, uint8_t* host, size_t n) {
     if (rc != ISING_OK) return rc;
     HIP_TRY(ctx, launch_bytes_to_canonical(planes_of(ctx->demon, ctx->L), reinterpret_cast<uint8_t*>(ctx->canon),
                                            ctx->stream));
-    HIP_TRY(ctx, hipMemcpyAsync(host, ctx->canon, N, hipMemcpyDeviceToHost, ctx->stream));
-    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+    HIP_TRY(ctx, copy_to_host(host, ctx->canon, N, ctx->stream));
     return ISING_OK;
 }
 
@@ -1556,6 +1558,7 @@ int ising_destroy(ising_ctx* ctx) {
     if (ctx->host_stage) (void)hipHostFree(ctx->host_stage);
     if (ctx->owns_stream && ctx->stream) (void)hipStreamDestroy(ctx->stream);
     (void)hipGetLastError();
+    hostcopy_release();
     delete ctx;
     return ISING_OK;
 }

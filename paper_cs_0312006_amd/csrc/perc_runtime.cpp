@@ -9,6 +9,7 @@
 #include <new>
 #include <vector>
 
+#include "ising_hostcopy.hpp"
 #include "perc_launch.hpp"
 #include "percolation.h"
 
@@ -266,7 +267,9 @@ int perc_create(const perc_params* params, void* stream, perc_ctx** out) {
     c->n_tx = (L + kTile - 1) / kTile;
     c->n_ty = c->n_tx;
     c->n_tiles = c->n_tx * c->n_ty;
+    ising::hostcopy_retain();
     if (hipGetDevice(&c->device) != hipSuccess) {
+        ising::hostcopy_release();
         delete c;
         return ISING_EDEVICE;
     }
@@ -274,6 +277,7 @@ int perc_create(const perc_params* params, void* stream, perc_ctx** out) {
         c->stream = (hipStream_t)stream;
     } else {
         if (hipStreamCreateWithFlags(&c->stream, hipStreamNonBlocking) != hipSuccess) {
+            ising::hostcopy_release();
             delete c;
             return ISING_EDEVICE;
         }
@@ -335,8 +339,7 @@ int perc_copy_medium(perc_ctx* c, uint8_t* host, size_t n) {
     if (rc != ISING_OK) return rc;
     if (!host || n < c->N) return ISING_EINVAL;
     if (!c->ran) return ISING_ESTATE;
-    PERC_TRY(c, hipMemcpyAsync(host, c->pore, c->N, hipMemcpyDeviceToHost, c->stream));
-    PERC_TRY(c, hipStreamSynchronize(c->stream));
+    PERC_TRY(c, ising::copy_to_host(host, c->pore, c->N, c->stream));
     return ISING_OK;
 }
 
@@ -345,8 +348,7 @@ int perc_copy_arrival(perc_ctx* c, int32_t* host, size_t n) {
     if (rc != ISING_OK) return rc;
     if (!host || n < c->N) return ISING_EINVAL;
     if (!c->ran) return ISING_ESTATE;
-    PERC_TRY(c, hipMemcpyAsync(host, c->arr, c->N * sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
-    PERC_TRY(c, hipStreamSynchronize(c->stream));
+    PERC_TRY(c, ising::copy_to_host(host, c->arr, c->N * sizeof(int32_t), c->stream));
     return ISING_OK;
 }
 
@@ -389,6 +391,7 @@ int perc_destroy(perc_ctx* c) {
     release(c->ws);
     if (c->owns_stream && c->stream) (void)hipStreamDestroy(c->stream);
     (void)hipGetLastError();
+    ising::hostcopy_release();
     delete c;
     return ISING_OK;
 }
