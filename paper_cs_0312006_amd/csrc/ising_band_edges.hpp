@@ -16,12 +16,24 @@ __device__ __forceinline__ void put_word(uint64_t* p, uint32_t tag, uint32_t w) 
     __hip_atomic_store(p, ((uint64_t)tag << 32) | w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The word at p once its tag is `tag` (the whole wave waits until every
-// lane's word has it). *err (host memory) is looked at only in long waits.
-__device__ __forceinline__ uint32_t take_word(const uint64_t* p, uint32_t tag, uint32_t* err) {
-    uint64_t v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// The words at p[0 .. N-1] once their tags are `tag` (the whole wave waits
+// until every lane's words have it). All N are read in every poll: their
+// latencies overlap. *err (host memory) is looked at only in long waits.
+template <int N>
+__device__ __forceinline__ void take_words(const uint64_t* const (&p)[N], uint32_t tag, uint32_t* err,
+                                           uint32_t (&out)[N]) {
     uint32_t polls = 0;
-    while (__ballot((uint32_t)(v >> 32) != tag)) {
+    for (;;) {
+        uint64_t v[N];
+        uint32_t miss = 0;
+#pragma unroll
+        for (int k = 0; k < N; ++k) v[k] = __hip_atomic_load(p[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            out[k] = (uint32_t)v[k];
+            miss |= (uint32_t)(v[k] >> 32) ^ tag;
+        }
+        if (__ballot(miss != 0u) == 0) break;
         if ((++polls & 255u) == 0u) {
             if (__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)) break;
             if (polls >= kBandMaxPolls) {
@@ -30,9 +42,14 @@ __device__ __forceinline__ uint32_t take_word(const uint64_t* p, uint32_t tag, u
             }
         }
         __builtin_amdgcn_s_sleep(1);
-        v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    return (uint32_t)v;
+}
+
+__device__ __forceinline__ uint32_t take_word(const uint64_t* p, uint32_t tag, uint32_t* err) {
+    const uint64_t* const ps[1] = {p};
+    uint32_t v[1];
+    take_words<1>(ps, tag, err, v);
+    return v[0];
 }
 
 }  // namespace

@@ -252,18 +252,18 @@ uint32_t bands_capacity(uint32_t threads, uint32_t lds_bytes, bool general, uint
 // against 3.18 (bytes), 2048 3.27 against 4.82 (bytes), 3072 5.6 against 6.8
 // (bits), 4096 7.1 against 8.44 (bits) and, h != 0, 9.38 (bytes). Larger
 // sides need more rows a band than a workgroup has waves, and stay bits.
-bool row_bands_serve(uint32_t L, uint32_t G) {
+bool row_bands_serve(uint32_t L, uint32_t G, bool creutz) {
     RowBandShape sh;
-    if (!row_band_shape(L, G, &sh)) return false;
+    if (!row_band_shape(L, G, creutz, &sh)) return false;
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
     static std::mutex mu;
-    static std::map<std::tuple<int, uint32_t, uint32_t>, bool> fits;
+    static std::map<std::tuple<int, uint32_t, uint32_t, bool>, bool> fits;
     std::lock_guard<std::mutex> lock(mu);
-    const auto key = std::make_tuple(dev, L, G);
+    const auto key = std::make_tuple(dev, L, G, creutz);
     auto it = fits.find(key);
     if (it == fits.end()) {
         int cus = 0, per = 0;
@@ -277,17 +277,26 @@ bool row_bands_serve(uint32_t L, uint32_t G) {
     return it->second;
 }
 
-hipError_t launch_bands(const BandArgs& a, uint32_t G, uint32_t threads, bool row_waves, hipStream_t s) {
+static hipError_t launch_row_bands(const BandArgs& a, uint32_t G, bool creutz, hipStream_t s) {
     BandArgs arg = a;
     void* args[] = {&arg};
-    if (a.n == 0) return hipErrorInvalidValue;
     RowBandShape sh;
-    if (row_waves && row_bands_serve(a.L, G) && row_band_shape(a.L, G, &sh)) {
-        const void* k = row_band_kernel(sh);
-        const hipError_t e = allow_lds(k, sh.lds);
-        if (e != hipSuccess) return e;
-        return hipLaunchCooperativeKernel(k, dim3(G), dim3(sh.threads), args, sh.lds, s);
-    }
+    if (a.n == 0 || !row_band_shape(a.L, G, creutz, &sh)) return hipErrorInvalidValue;
+    const void* k = row_band_kernel(sh);
+    const hipError_t e = allow_lds(k, sh.lds);
+    if (e != hipSuccess) return e;
+    return hipLaunchCooperativeKernel(k, dim3(G), dim3(sh.threads), args, sh.lds, s);
+}
+
+hipError_t launch_creutz_bands(const BandArgs& a, uint32_t G, hipStream_t s) {
+    return launch_row_bands(a, G, true, s);
+}
+
+hipError_t launch_bands(const BandArgs& a, uint32_t G, uint32_t threads, bool row_waves, hipStream_t s) {
+    if (a.n == 0) return hipErrorInvalidValue;
+    if (row_waves && row_bands_serve(a.L, G, false)) return launch_row_bands(a, G, false, s);
+    BandArgs arg = a;
+    void* args[] = {&arg};
     if (a.L % 8u != 0u || G < 2u || G > a.L || a.Wr == 0 || a.Wr > kBandMaxWr || threads % 64u != 0 || threads == 0 ||
         threads > 64u * kBandMaxWaves)
         return hipErrorInvalidValue;

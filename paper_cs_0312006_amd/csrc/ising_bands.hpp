@@ -24,6 +24,9 @@ struct BandArgs {
     uint32_t general;   // 1: the (s, m) classes (h != 0), 0: the two h = 0 classes
     BitsLattice bl;
     AcceptTable at;     // the acceptance table (a wave per row)
+    uint32_t* d0;       // Creutz: demon planes, updated in place
+    uint32_t* d1;
+    uint32_t rev;       // Creutz: 1 runs colour 1 first (reversed sweeps)
 };
 
 // A wave sweeps a band row in chunks of 64 words (a word per lane); rows of
@@ -37,20 +40,24 @@ inline uint32_t band_lds_bytes(uint32_t L, uint32_t G, uint32_t Wr) { return 2u 
 // Workgroups of `threads` threads that can be resident at once for bands of
 // lds_bytes each and rows of Wr words (0 on error).
 uint32_t bands_capacity(uint32_t threads, uint32_t lds_bytes, bool general, uint32_t Wr);
-// Bands of a wave per row (ising_band_rows.hip): words a lane, how rows end
+// Bands of a wave per row (ising_band_rows.hpp): words a lane, how rows end
 // (kRows*), half-sweeps between exchanges, threads and LDS of a workgroup.
 struct RowBandShape {
     uint32_t cw, mode, depth, threads, lds;
+    bool creutz;  // Creutz dynamics (else Metropolis)
 };
 // The shape for G bands of side L (any even side); false if a row does not
 // fit a wave or a band with its outside rows does not fit a workgroup.
-bool row_band_shape(uint32_t L, uint32_t G, RowBandShape* out);
+bool row_band_shape(uint32_t L, uint32_t G, bool creutz, RowBandShape* out);
 const void* row_band_kernel(const RowBandShape& s);
+const void* creutz_row_kernel(const RowBandShape& s);
 // Tagged words its edge slots and load flags take (0 if not served).
-size_t row_band_pub_words(uint32_t L, uint32_t G);
+size_t row_band_pub_words(uint32_t L, uint32_t G, bool creutz);
 // Whether G bands of side L run with a wave per row on the current device.
-bool row_bands_serve(uint32_t L, uint32_t G);
+bool row_bands_serve(uint32_t L, uint32_t G, bool creutz);
 
+// Creutz sweeps of G bands, a wave per row (row_bands_serve).
+hipError_t launch_creutz_bands(const BandArgs& a, uint32_t G, hipStream_t s);
 // One cooperative launch of G band workgroups, a wave per row where
 // `row_waves` and row_bands_serve allow it, else bits with `threads` threads
 // (L % 8 == 0 only).

@@ -174,7 +174,8 @@ static bool bands_fit(uint32_t L, uint32_t rows, uint32_t per_wave) {
 // Default band height: about one band per compute unit, but at least four
 // rows (a band of four trades its edges every four half-sweeps, one of two
 // every two: 256^2 1.60 us a sweep with four rows, 1.95 with two, 2.56 with
-// one; 512^2 1.57 and 1.98), and 16 rows rather than 12 to 15 (no rows
+// one; 512^2 1.57 and 1.98; every band: 1002^2 takes five rows, not bands of
+// three and four), and 16 rows rather than 12 to 15 (no rows
 // outside the band to update: 3072^2 5.6 us with 16, 5.9 with 12; eight to
 // eleven rows measure the same as 16 or better).
 static uint32_t band_default_rows(uint32_t L) {
@@ -184,7 +185,8 @@ static uint32_t band_default_rows(uint32_t L) {
         (void)hipGetLastError();
         cus = 256;
     }
-    const uint32_t rows = std::max<uint32_t>(4u, (L + (uint32_t)cus - 1u) / (uint32_t)cus);
+    uint32_t rows = std::max<uint32_t>(4u, (L + (uint32_t)cus - 1u) / (uint32_t)cus);
+    while (rows < 8u && L / band_count(L, rows) < 4u && L >= 8u) ++rows;  // the lowest band has four rows too
     return std::min<uint32_t>(rows > 11u && rows < 16u ? 16u : rows, std::max<uint32_t>(1u, L / 2u));
 }
 
@@ -331,13 +333,12 @@ int ctx_reserve_series(ising_ctx* ctx, uint64_t more) {
 // Tagged edge-row words for G bands of side L, whichever kernel runs them.
 static size_t band_slot_words(uint32_t L, uint32_t G) {
     const size_t bits = L % 8u == 0u ? band_pub_words(G, band_words(L)) : 0;
-    return std::max(bits, row_band_pub_words(L, G));
+    return std::max(bits, row_band_pub_words(L, G, false));
 }
 
-// The band plan's edge-row slots for G bands and its timeout mark (the
+// `words` tagged edge-row words for band launches, and their timeout mark (the
 // slots only grow; growing waits for the launches that may still use them).
-static int ctx_band_slots(ising_ctx* ctx, uint32_t G) {
-    const size_t words = band_slot_words(ctx->L, G);
+static int ctx_band_slots(ising_ctx* ctx, size_t words) {
     if (words > ctx->band_words) {
         if (ctx->band_words) HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
         if (ctx->band_pub) (void)hipFree(ctx->band_pub);
@@ -394,7 +395,7 @@ static int ctx_band_part(ising_ctx* ctx, uint32_t G) {
 static uint32_t generic_bands(const ising_ctx* ctx) {
     if (ctx->plan.kind != ISING_PLAN_GENERIC || ctx->L % 8u == 0u) return 0;
     const uint32_t G = band_count(ctx->L, band_default_rows(ctx->L));
-    return row_bands_serve(ctx->L, G) ? G : 0;
+    return row_bands_serve(ctx->L, G, false) ? G : 0;
 }
 
 // Whether a call of n sweeps on a resident-plan context of a side the plan
@@ -406,7 +407,7 @@ static uint32_t generic_bands(const ising_ctx* ctx) {
 static bool resident_on_bands(const ising_ctx* ctx, uint64_t n) {
     const uint64_t sites = (uint64_t)ctx->L * ctx->L;
     return ctx->L <= kResidentMaxL && sites > 4400u && n * (sites - 4400u) >= 100000u &&
-           row_bands_serve(ctx->L, band_count(ctx->L, band_default_rows(ctx->L)));
+           row_bands_serve(ctx->L, band_count(ctx->L, band_default_rows(ctx->L)), false);
 }
 
 // Allocate what the context's plan needs: the second lattice buffer for
@@ -422,11 +423,11 @@ int ctx_prepare_plan(ising_ctx* ctx) {
         ctx->owns_buf[1] = true;
     }
     if (ctx->plan.kind == ISING_PLAN_BANDS) {
-        const int rc = ctx_band_slots(ctx, band_count(ctx->L, ctx->plan.rows));
+        const int rc = ctx_band_slots(ctx, band_slot_words(ctx->L, band_count(ctx->L, ctx->plan.rows)));
         if (rc != ISING_OK) return rc;
     }
     if (const uint32_t G = generic_bands(ctx)) {
-        int rc = ctx_band_slots(ctx, G);
+        int rc = ctx_band_slots(ctx, band_slot_words(ctx->L, G));
         if (rc == ISING_OK) rc = ctx_band_part(ctx, G);  // here: ising_sweep_static may not allocate
         if (rc != ISING_OK) return rc;
     }
@@ -485,6 +486,15 @@ static int sweep_fused(ising_ctx* ctx, uint64_t n, int64_t* ser, int64_t* part0,
     return ISING_OK;
 }
 
+// Tags for a launch of m sweeps: where they would wrap, clear every slot and
+// count from 0 again.
+static int ctx_band_tags(ising_ctx* ctx, uint32_t m) {
+    if ((uint64_t)ctx->band_base + 2ull * m < 0xffffffffull) return ISING_OK;
+    HIP_TRY(ctx, launch_bands_clear(ctx->band_pub, ctx->band_words, ctx->stream));
+    ctx->band_base = 0;
+    return ISING_OK;
+}
+
 // n sweeps of the band plan with bands of `rows` rows, `per_wave` rows a
 // wave: launches of up to `chunk` sweeps, each followed by the sum of its
 // bands' partials (at part) into ser.
@@ -509,11 +519,8 @@ static int sweep_bands(ising_ctx* ctx, uint64_t n, int64_t* ser, int64_t* part, 
     a.at = ctx->table;
     for (uint64_t done = 0; done < n;) {
         const uint32_t m = (uint32_t)std::min<uint64_t>(n - done, chunk);
-        if ((uint64_t)ctx->band_base + 2ull * m >= 0xffffffffull) {
-            // the tags would wrap: clear every slot and count from 0 again
-            HIP_TRY(ctx, launch_bands_clear(ctx->band_pub, ctx->band_words, ctx->stream));
-            ctx->band_base = 0;
-        }
+        const int rc = ctx_band_tags(ctx, m);
+        if (rc != ISING_OK) return rc;
         a.t0 = (uint32_t)(ctx->t + done);
         a.n = m;
         a.base = ctx->band_base;
@@ -794,7 +801,7 @@ int ising_sweep(ising_ctx* ctx, uint64_t n) {
     ++ctx->gen;
     if (ctx->plan.kind == ISING_PLAN_RESIDENT && resident_on_bands(ctx, n) && !stream_capturing(ctx->stream)) {
         const uint32_t rows = band_default_rows(ctx->L), G = band_count(ctx->L, rows);
-        rc = ctx_band_slots(ctx, G);
+        rc = ctx_band_slots(ctx, band_slot_words(ctx->L, G));
         if (rc == ISING_OK) rc = ctx_band_part(ctx, G);
         if (rc == ISING_OK)
             rc = sweep_bands(ctx, n, ctx->series + 2 * ctx->series_len, ctx->band_part, kBandChunk, rows, 1u);
@@ -936,7 +943,7 @@ static int lone_band_batch(ising_ctx* ctx, uint64_t n, hipStream_t s) {
     if (!plan_for(ctx->L, ISING_PLAN_BANDS, 0, 0, &bp)) return ISING_EUNSUPPORTED;
     const uint32_t G = band_count(ctx->L, bp.rows);
     if ((rc = ctx_reserve_series(ctx, n)) != ISING_OK) return rc;
-    if ((rc = ctx_band_slots(ctx, G)) != ISING_OK) return rc;
+    if ((rc = ctx_band_slots(ctx, band_slot_words(ctx->L, G))) != ISING_OK) return rc;
     if ((rc = ctx_band_part(ctx, G)) != ISING_OK) return rc;
     const bool other = s && s != ctx->stream;
     struct Ev {
@@ -1469,6 +1476,45 @@ static int creutz_sweep_fused(ising_ctx* ctx, uint64_t n, uint32_t cw, uint32_t 
     return ISING_OK;
 }
 
+// n Creutz sweeps on bands, a wave per row: both directions, any side whose
+// rows fit. *served is false when the call is left to the streaming kernels:
+// large sides, captured streams, calls of one or two sweeps (a cooperative
+// launch costs about 12 us more than they save), no room for the buffers.
+static int creutz_sweep_bands(ising_ctx* ctx, uint64_t n, bool reverse, int64_t* ser, bool* served) {
+    *served = false;
+    const uint32_t L = ctx->L;
+    if (n < 3 || stream_capturing(ctx->stream)) return ISING_OK;
+    const uint32_t G = band_count(L, band_default_rows(L));
+    if (!row_bands_serve(L, G, true)) return ISING_OK;
+    int rc = ctx_band_slots(ctx, row_band_pub_words(L, G, true));
+    if (rc == ISING_OK) rc = ctx_band_part(ctx, G);
+    if (rc == ISING_ENOMEM) return ISING_OK;
+    if (rc != ISING_OK) return rc;
+    const Planes pl = ctx_planes(ctx), dm = planes_of(ctx->demon, L);
+    BandArgs a{};
+    a.p0 = reinterpret_cast<uint32_t*>(pl.p[0]);
+    a.p1 = reinterpret_cast<uint32_t*>(pl.p[1]);
+    a.d0 = reinterpret_cast<uint32_t*>(dm.p[0]);
+    a.d1 = reinterpret_cast<uint32_t*>(dm.p[1]);
+    a.L = L;
+    a.pub = ctx->band_pub;
+    a.part = ctx->band_part;
+    a.err = ctx->band_err;
+    a.rev = reverse ? 1u : 0u;
+    for (uint64_t done = 0; done < n;) {
+        const uint32_t m = (uint32_t)std::min<uint64_t>(n - done, kBandChunk);
+        if ((rc = ctx_band_tags(ctx, m)) != ISING_OK) return rc;
+        a.n = m;
+        a.base = ctx->band_base;
+        HIP_TRY(ctx, launch_creutz_bands(a, G, ctx->stream));
+        ctx->band_base += 2u * m;
+        HIP_TRY(ctx, launch_bands_reduce(ctx->band_part, G, m, ser + 2 * done, ctx->stream));
+        done += m;
+    }
+    *served = true;
+    return ISING_OK;
+}
+
 int ising_creutz_sweep(ising_ctx* ctx, uint64_t n, int reverse) {
     int rc = ctx_enter(ctx);
     if (rc != ISING_OK) return rc;
@@ -1478,6 +1524,13 @@ int ising_creutz_sweep(ising_ctx* ctx, uint64_t n, int reverse) {
     if (rc != ISING_OK) return rc;
     ++ctx->gen;
     int64_t* ser = ctx->series + 2 * ctx->series_len;
+    bool served = false;
+    rc = creutz_sweep_bands(ctx, n, reverse != 0, ser, &served);
+    if (rc != ISING_OK) return rc;
+    if (served) {
+        ctx->series_len += n;
+        return ISING_OK;
+    }
     uint32_t cw = 0, rows = 0;
     if (!reverse && ctx->L % 8u == 0u && default_fused(ctx->L, &cw, &rows)) {
         rc = creutz_fused_prepare(ctx, cw, rows);
