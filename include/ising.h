@@ -64,7 +64,7 @@ extern "C" {
 
 /* Plan selection (ising_params.flags, low byte). AUTO picks per lattice side:
  * the workgroup-resident kernel for small sides, the band-resident plan for
- * sides 136 to 16384 (about one band of rows per compute unit), the fused
+ * sides 96 to 16384 (about one band of rows per compute unit), the fused
  * one-pass sweep by full-row workgroups where a row fits one workgroup, the
  * fused sweep by wave tiles for larger sides, the two-pass in-place sweep
  * otherwise. The others force a path (ISING_EUNSUPPORTED if the side does
@@ -72,11 +72,9 @@ extern "C" {
 #define ISING_PLAN_AUTO 0u
 #define ISING_PLAN_TWO_PASS 1u  /* one launch per colour, in place */
 #define ISING_PLAN_FUSED 2u     /* one launch per sweep, ping-pong buffers; a wave per tile */
-#define ISING_PLAN_RESIDENT 3u  /* one workgroup runs all sweeps of the call (sides 72 to 128: bands, from
-                                   * the length of call at which they are faster) */
+#define ISING_PLAN_RESIDENT 3u  /* one workgroup runs all sweeps of the call */
 #define ISING_PLAN_GENERIC 4u   /* the only plan for L % 8 != 0: bands as below where a row fits a wave
-                                   * (L up to 4086), else, for single sweeps of small lattices and under
-                                   * stream capture, per-site draws */
+                                   * (L up to 4086), else, and under stream capture, per-site draws */
 #define ISING_PLAN_FUSED_ROWS 5u /* as FUSED, a workgroup per band of whole rows (L/8 <= 16 * 64 * cw) */
 #define ISING_PLAN_BANDS 6u      /* the lattice split into bands of whole rows, one workgroup each, all
                                    * resident at once; each band stays on chip for every sweep of a
@@ -228,7 +226,7 @@ int ising_load_spins(ising_ctx* ctx, const int8_t* host, size_t n, uint64_t t);
  * predicted slower, graph replays of passes that spread every lattice over
  * the whole GPU. The descriptors are staged through pinned host
  * memory by one copy kernel. A batch with a single lattice to sweep whose
- * side the band-resident plan serves by default (136 to 16384) runs on that
+ * side the band-resident plan serves by default (96 to 16384) runs on that
  * plan instead, on the context's stream ordered after `stream`'s earlier
  * work and before its later work (neither batch plan can spread one lattice
  * over the chip). Lattices may differ in L, J, h, T and seed;

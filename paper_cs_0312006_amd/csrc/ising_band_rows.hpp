@@ -70,6 +70,7 @@
 #include "ising_bands.hpp"
 #include "ising_creutz.hpp"
 #include "ising_fused_core.hpp"
+#include "ising_site_draws.hpp"
 
 namespace ising {
 
@@ -78,58 +79,6 @@ namespace {
 constexpr int kRowsFull = 0, kRowsRagged = 1, kRowsShifted = 2;
 constexpr uint32_t kMaxRowWaves = 16;
 constexpr uint32_t kFlushSweeps = 32;  // sweeps whose wave sums are kept in LDS between flushes
-
-// The parts of the Philox4x32-10 calls of quad q that do not depend on the
-// sweep. With key (k0, k1), counter (q, t, c, 0) and W the key increments:
-//   round 1: x = (t ^ k0, c M1, hi(M0 q) ^ k1, lo(M0 q))      (c < 2: hi(M1 c) = 0)
-//   round 2: x = (hi(M1 x2) ^ c M1 ^ k0 + W0, lo(M1 x2), hi(M0 (t ^ k0)) ^ lo(M0 q) ^ k1 + W1, lo(M0 (t ^ k0)))
-//   round 3: x = (hi(M1 x2) ^ x1 ^ k0 + 2 W0, lo(M1 x2), hi(M0 x0) ^ x3 ^ k1 + 2 W1, lo(M0 x0))
-// so lo(M0 q) (a), the second round's x1 with round 3's key (b) and the
-// third round's product M0 x0 (p, one for each colour) are fixed.
-struct SiteDraws {
-    uint32_t a, b;
-};
-
-__device__ __forceinline__ SiteDraws site_draws(uint32_t q, uint32_t k0, uint32_t k1, uint32_t& x0_c0) {
-    const uint64_t p0 = mul_u64(q, kPhiloxM0);
-    const uint64_t p1 = mul_u64((uint32_t)(p0 >> 32) ^ k1, kPhiloxM1);
-    x0_c0 = (uint32_t)(p1 >> 32) ^ (k0 + kPhiloxW0);  // colour 0; colour 1: ^ M1
-    return {(uint32_t)p0, (uint32_t)p1 ^ (k0 + 2u * kPhiloxW0)};
-}
-
-// The wave-uniform parts of a half-sweep's calls.
-struct SweepDraws {
-    uint32_t u, v;
-};
-__device__ __forceinline__ SweepDraws sweep_draws(uint32_t t, uint32_t k0, uint32_t k1) {
-    const uint64_t p = (uint64_t)kPhiloxM0 * (t ^ k0);
-    return {(uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(p >> 32) ^ (k1 + kPhiloxW1))),
-            (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)p ^ (k1 + 2u * kPhiloxW1)))};
-}
-
-// The four draws from the fixed parts: p is M0 times the second round's x0.
-__device__ __forceinline__ uint4 philox_fixed(const SiteDraws& f, uint64_t p, const SweepDraws& s, uint32_t k0,
-                                              uint32_t k1) {
-    const uint64_t p1 = mul_u64(f.a ^ s.u, kPhiloxM1);
-    uint32_t x0 = (uint32_t)(p1 >> 32) ^ f.b, x1 = (uint32_t)p1;
-    uint32_t x2 = (uint32_t)(p >> 32) ^ s.v, x3 = (uint32_t)p;
-    k0 += 3u * kPhiloxW0;
-    k1 += 3u * kPhiloxW1;
-#pragma unroll
-    for (int r = 3; r < 10; ++r) {
-        const uint64_t q0 = (uint64_t)kPhiloxM0 * x0, q1 = (uint64_t)kPhiloxM1 * x2;
-        const uint32_t rk0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)k0);
-        const uint32_t rk1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)k1);
-        const uint32_t y0 = xor3((uint32_t)(q1 >> 32), x1, rk0), y2 = xor3((uint32_t)(q0 >> 32), x3, rk1);
-        x1 = (uint32_t)q1;
-        x3 = (uint32_t)q0;
-        x0 = y0;
-        x2 = y2;
-        k0 += kPhiloxW0;
-        k1 += kPhiloxW1;
-    }
-    return make_uint4(x0, x1, x2, x3);
-}
 
 // A row's words as bits (site b of word j at 4 j + b), and back.
 template <int CW>
@@ -145,18 +94,6 @@ __device__ __forceinline__ Row<CW> row_of_bits(uint32_t v) {
 #pragma unroll
     for (int j = 0; j < CW; ++j) r.v[j] = (((v >> (4 * j)) & 0xfu) * 0x00204081u) & 0x01010101u;
     return r;
-}
-
-// Sum over the wave, valid in lane 63 (whole-wave DPP reduction: no LDS
-// round trips on the path between two barriers).
-__device__ __forceinline__ uint32_t wave_sum_lane63(uint32_t v) {
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true);   // row_shr:1
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true);   // row_shr:2
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true);   // row_shr:4
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true);   // row_shr:8
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);  // row_bcast:15
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);  // row_bcast:31
-    return v;
 }
 
 // Tagged words a lane publishes of a row: its bits (both colours from D = 2

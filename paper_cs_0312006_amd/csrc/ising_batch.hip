@@ -8,6 +8,9 @@
 // the kernel is persistent: no workgroup waits on another.
 //
 // Where a lattice lives while it is swept:
+//   - lattices of at most four byte words of a colour per thread (sides up to
+//     176) stay in registers, with a copy in LDS for the neighbours
+//     (run_small);
 //   - lattices whose two colour planes fit this workgroup's LDS at one bit
 //     per site (sides up to 1072) are converted to bits, swept there for all
 //     their sweeps and converted back (the bit-packed path below): h = 0
@@ -21,6 +24,8 @@
 #include "ising_bits.hpp"
 #include "ising_device.hpp"
 #include "ising_launch.hpp"
+#include "ising_fused_core.hpp"
+#include "ising_site_draws.hpp"
 
 namespace ising {
 
@@ -120,6 +125,126 @@ __device__ __forceinline__ void run_lattice(const LdsTable& lt, const BatchItem&
     }
     const uint32_t rem = it.n % kFlush;
     if (rem) flush(it.n - rem, rem);
+}
+
+// The smallest lattices: a thread keeps K words of each colour in registers
+// for all sweeps (a copy in LDS serves the neighbours), with their Philox
+// calls' sweep-independent parts (ising_site_draws.hpp), and draws for a
+// word's next update before the barrier that precedes it (drawing in two
+// parts behind the two LDS reads of an update measured 4-20% slower). What
+// bounds such a lattice is the latency of a half-sweep: a barrier, an LDS
+// read of three neighbour words, the table read, 45 operations a word. In bits most
+// threads would idle (64^2 holds 64 words a colour). Against the loop over
+// chunks below, us a sweep of one lattice: 64^2 0.50 against 1.40, 96^2 0.83
+// against 2.35, 128^2 1.16 against 3.69.
+template <int K>
+__device__ __forceinline__ void run_small(const LdsTable& lt, const BatchItem& it, uint32_t* __restrict__ lat,
+                                          uint32_t (*part)[kMaxWaves][2]) {
+    const uint32_t L = it.L, Hw = it.Hw, total = L * Hw, k0 = it.k0, k1 = it.k1;
+    const uint32_t lane = threadIdx.x & 63u, wv = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
+    uint32_t* const l0 = lat;
+    uint32_t* const l1 = lat + total;
+    global_u32* const g0 = as_global(it.p0);
+    global_u32* const g1 = as_global(it.p1);
+    // per word: its place, its neighbours' in the other plane (the same row's
+    // outer word depends on the colour), the same row's side
+    uint32_t at[K], up[K], dn[K], e0[K], e1[K], odd[K], own0[K], own1[K];
+    bool valid[K];
+    SiteDraws sd[K];
+    uint64_t pr0[K], pr1[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const uint32_t w = threadIdx.x + (uint32_t)k * blockDim.x;
+        valid[k] = w < total;
+        at[k] = valid[k] ? w : 0u;
+        const uint32_t i = at[k] / Hw, x = at[k] - i * Hw;
+        up[k] = (i == 0u ? L - 1u : i - 1u) * Hw + x;
+        dn[k] = (i + 1u == L ? 0u : i + 1u) * Hw + x;
+        const uint32_t nx = i * Hw + (x + 1u == Hw ? 0u : x + 1u), pv = i * Hw + (x == 0u ? Hw - 1u : x - 1u);
+        odd[k] = i & 1u;
+        e0[k] = odd[k] ? nx : pv;  // colour c of row i: the next word where i + c is odd
+        e1[k] = odd[k] ? pv : nx;
+        own0[k] = g0[at[k]];
+        own1[k] = g1[at[k]];
+        if (valid[k]) {
+            l0[w] = own0[k];
+            l1[w] = own1[k];
+        }
+        uint32_t x0;
+        sd[k] = site_draws(at[k], k0, k1, x0);
+        pr0[k] = mul_u64(x0, kPhiloxM0);
+        pr1[k] = mul_u64(x0 ^ kPhiloxM1, kPhiloxM0);
+    }
+    uint4 rr[K];
+    auto draw = [&](auto cc, uint32_t t) {
+        const SweepDraws s = sweep_draws(t, k0, k1);
+#pragma unroll
+        for (int k = 0; k < K; ++k) rr[k] = philox_fixed(sd[k], decltype(cc)::value ? pr1[k] : pr0[k], s, k0, k1);
+    };
+    uint32_t sums = 0;
+    auto half = [&](auto cc) {
+        constexpr bool C = decltype(cc)::value == 1;
+        const uint32_t* const oth = C ? l0 : l1;
+        uint32_t U[K], D[K], E[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            U[k] = oth[up[k]];
+            D[k] = oth[dn[k]];
+            E[k] = oth[C ? e1[k] : e0[k]];
+        }
+        uint32_t sad = 0, ups = 0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            uint32_t& own = C ? own1[k] : own0[k];
+            const uint32_t same = C ? own0[k] : own1[k];
+            const bool right = (odd[k] != 0u) != C;  // the same-row neighbour is the next site
+            const uint32_t S = __builtin_amdgcn_alignbyte(right ? E[k] : same, right ? same : E[k], right ? 1u : 3u);
+            const uint32_t n = U[k] + D[k] + S + same;
+            const AcceptEntries ent = accept_entries(lt, (own << 3) + n);
+            own = accept_from(ent, rr[k]);
+            if (valid[k]) (C ? l1 : l0)[at[k]] = own;
+            if (C && valid[k]) {
+                sad = sad_misaligned(own, n, sad);
+                ups += own + same;
+            }
+        }
+        if (C) sums = sad | (__builtin_amdgcn_sad_u8(ups, 0u, 0u) << 16);
+    };
+    auto flush = [&](uint32_t first, uint32_t count) {
+        if (threadIdx.x < count) {
+            const uint32_t slot = (first + threadIdx.x) % kFlush;
+            int64_t ss = 0, su = 0;
+            for (uint32_t w = 0; w < nwaves; ++w) {
+                ss += part[slot][w][0] & 0xffffu;
+                su += part[slot][w][0] >> 16;
+            }
+            it.series[2 * (first + threadIdx.x)] = 16 * (int64_t)total - 2 * ss;
+            it.series[2 * (first + threadIdx.x) + 1] = 2 * su - 8 * (int64_t)total;
+        }
+    };
+    draw(Step<0>{}, it.t0);
+    __syncthreads();
+    for (uint32_t s = 0; s < it.n; ++s) {
+        const uint32_t t = it.t0 + s;
+        half(Step<0>{});
+        draw(Step<1>{}, t);
+        __syncthreads();
+        half(Step<1>{});
+        // a wave's sums fit 16 bits each (sad <= 16 K a lane, ups <= 8 K)
+        const uint32_t both = wave_sum_lane63(sums);
+        if (lane == 63u) part[s % kFlush][wv][0] = both;
+        draw(Step<0>{}, t + 1u);
+        __syncthreads();
+        if ((s + 1) % kFlush == 0) flush(s + 1 - kFlush, kFlush);
+    }
+    const uint32_t rem = it.n % kFlush;
+    if (rem) flush(it.n - rem, rem);
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        if (valid[k]) {
+            g0[at[k]] = own0[k];
+            g1[at[k]] = own1[k];
+        }
 }
 
 // The bit layout and the word update are those of ising_bits.hpp.
@@ -268,7 +393,12 @@ __device__ __forceinline__ void batch_one(const BatchItem& it, LdsTable& lt, uin
     __syncthreads();
     const uint32_t plane_words = it.L * it.Hw;
     const uint32_t bit_words = it.L * ((it.Hw + 7u) / 8u);
-    if (it.bits && 2u * bit_words * 4u <= kBatchBitsLdsBytes && it.n > 0) {
+    const uint32_t per_thread = (plane_words + blockDim.x - 1u) / blockDim.x;
+    if (per_thread <= 4u && it.n > 0) {
+        if (per_thread == 1u) run_small<1>(lt, it, lat, red);
+        else if (per_thread == 2u) run_small<2>(lt, it, lat, red);
+        else run_small<4>(lt, it, lat, red);
+    } else if (it.bits && 2u * bit_words * 4u <= kBatchBitsLdsBytes && it.n > 0) {
         bits_load(lat, it, (it.Hw + 7u) / 8u);
         __syncthreads();
         if (it.bits == 3u) run_bits<true>(lat, it, red);
@@ -376,7 +506,10 @@ hipError_t launch_stage_copy(void* dst, const void* host_src, size_t bytes, hipS
 }
 
 hipError_t launch_batch_one(const BatchItem& it, hipStream_t s) {
-    k_batch_one<<<1, kBatchThreads, 0, s>>>(it);
+    // no more waves than words: idle ones only lengthen the barriers
+    const uint32_t words = it.L * it.Hw;
+    const uint32_t threads = words < kBatchThreads ? (words + 63u) / 64u * 64u : kBatchThreads;
+    k_batch_one<<<1, threads, 0, s>>>(it);
     return hipGetLastError();
 }
 

@@ -67,9 +67,9 @@ struct Rates {
 const Rates kDefaultRates = {
     false,
     // resident, per workgroup: bands 128, 256, 512, 1072, larger; h = 0 then h != 0
-    {5.45, 4.05, 8.59, 6.08, 9.06, 6.05, 9.02, 6.31, 5.11, 5.12},
+    {7.6, 7.5, 8.59, 6.08, 9.06, 6.05, 9.02, 6.31, 5.11, 5.12},
     // resident, fixed ns per lattice
-    {72e3, 104e3, 147e3, 118e3, 169e3, 187e3, 381e3, 406e3, 20e3, 22e3},
+    {62e3, 42e3, 147e3, 118e3, 169e3, 187e3, 381e3, 406e3, 20e3, 22e3},
     // stepped, tile rows 8, 16, 32
     {{323, 220, 138}, {318, 220, 137},
      {841, 758, 505}, {841, 756, 502},

@@ -75,8 +75,9 @@ static bool valid_params(const ising_params* p) {
 static std::mutex g_tuned_mu;
 static std::map<uint32_t, Plan> g_tuned;
 
-// Sides up to this run all their sweeps inside one workgroup by default.
-constexpr uint32_t kResidentMaxL = 128;
+// Sides up to this run all their sweeps inside one workgroup by default (88^2:
+// 1.13 us a sweep against 1.38 on bands, 96^2 1.9 against 1.42).
+constexpr uint32_t kResidentMaxL = 88;
 // Fused tiles wanted per launch (one wave each) before a taller/wider tile is used.
 constexpr uint32_t kFusedMinTiles = 16384;
 // The autotuner replaces the default plan only when a candidate is faster
@@ -84,7 +85,15 @@ constexpr uint32_t kFusedMinTiles = 16384;
 constexpr float kTuneMargin = 0.03f;
 // Band plan: sides it serves by default, and sweeps per launch (the
 // partials of a launch are bands x sweeps pairs).
-constexpr uint32_t kBandMinDefaultL = 136;
+constexpr uint32_t kBandMinDefaultL = 96;
+// Short calls of small band-plan lattices run in one workgroup: a cooperative
+// launch and the sum of its partials cost about 10 us more than its launch.
+// At 96 to 128 the bands win from about 20 sweeps (a call of 10: 49 against
+// 56 us; 1.9 against 1.4 us a sweep), up to 184 from three (one sweep: 35
+// against 44 us; three: 47 each), above from the first.
+static bool short_band_call(uint32_t L, uint64_t n) {
+    return L >= kBandMinDefaultL && ((L <= 128u && n < 20u) || (L <= 184u && n <= 2u));
+}
 constexpr uint32_t kBandChunk = ISING_BAND_SWEEPS_PER_LAUNCH;
 constexpr uint32_t kTuneRounds = 3;
 
@@ -398,18 +407,6 @@ static uint32_t generic_bands(const ising_ctx* ctx) {
     return row_bands_serve(ctx->L, G, false) ? G : 0;
 }
 
-// Whether a call of n sweeps on a resident-plan context of a side the plan
-// is the default for runs on bands instead. One workgroup sweeps in about
-// 0.67 + 1.8e-4 L^2 us, bands of four rows in 1.5 us at any of these sides,
-// but a band call costs about 12 us more around its sweeps (a cooperative
-// launch, the sum of its partials): at 128 the bands win from 7 sweeps up
-// (398.7 against 191.3 us for 100), at 96 from 15, at 72 from 60, at 64 never.
-static bool resident_on_bands(const ising_ctx* ctx, uint64_t n) {
-    const uint64_t sites = (uint64_t)ctx->L * ctx->L;
-    return ctx->L <= kResidentMaxL && sites > 4400u && n * (sites - 4400u) >= 100000u &&
-           row_bands_serve(ctx->L, band_count(ctx->L, band_default_rows(ctx->L)), false);
-}
-
 // Allocate what the context's plan needs: the second lattice buffer for
 // ping-pong, partial-sum buffers sized to the plan's tiles or blocks.
 int ctx_prepare_plan(ising_ctx* ctx) {
@@ -648,8 +645,8 @@ static int sweep_replays(ising_ctx* ctx, uint64_t n, uint64_t* left) {
 
 static int sweep_generic(ising_ctx* ctx, uint64_t n, int64_t* ser) {
     // not under capture: a band launch's tags advance on the host. One sweep
-    // of a small lattice is faster as its three per-site launches (37 against
-    // 44 us for the call at 66^2; from two sweeps the bands win, 46 against 70).
+    // of a small lattice is faster as its three per-site launches (38 against
+    // 46 us for the call at 66^2; from two sweeps the bands win, 46 against 61).
     const bool direct = (n == 1 && ctx->L <= 256u) || stream_capturing(ctx->stream);
     const uint32_t G = direct ? 0 : generic_bands(ctx);
     if (G && ctx->band_part_cap >= G)
@@ -799,19 +796,7 @@ int ising_sweep(ising_ctx* ctx, uint64_t n) {
     rc = ctx_reserve_series(ctx, n);
     if (rc != ISING_OK) return rc;
     ++ctx->gen;
-    if (ctx->plan.kind == ISING_PLAN_RESIDENT && resident_on_bands(ctx, n) && !stream_capturing(ctx->stream)) {
-        const uint32_t rows = band_default_rows(ctx->L), G = band_count(ctx->L, rows);
-        rc = ctx_band_slots(ctx, band_slot_words(ctx->L, G));
-        if (rc == ISING_OK) rc = ctx_band_part(ctx, G);
-        if (rc == ISING_OK)
-            rc = sweep_bands(ctx, n, ctx->series + 2 * ctx->series_len, ctx->band_part, kBandChunk, rows, 1u);
-        if (rc == ISING_OK) {
-            ctx->t += n;
-            ctx->series_len += n;
-        }
-        if (rc != ISING_ENOMEM) return rc;  // no room for the bands' buffers: one workgroup does it
-    }
-    if (ctx->plan.kind == ISING_PLAN_RESIDENT) {
+    if (ctx->plan.kind == ISING_PLAN_RESIDENT || (ctx->plan.kind == ISING_PLAN_BANDS && short_band_call(ctx->L, n))) {
         // one workgroup runs every sweep from local memory (bytes: a lone
         // lattice's latency, not the chip's throughput, sets the time)
         BatchItem it;
@@ -832,13 +817,7 @@ int ising_sweep(ising_ctx* ctx, uint64_t n) {
         case ISING_PLAN_GENERIC: rc = sweep_generic(ctx, n, ser); break;
         case ISING_PLAN_BANDS:
             rc = ctx_band_part(ctx, band_count(ctx->L, ctx->plan.rows));
-            // one or two sweeps of a side below 192: a launch per colour costs
-            // less than a cooperative launch (136: 35 and 42 us a call against
-            // 44 and 45; three sweeps and more, or 192 and up, bands)
-            if (rc == ISING_OK && n <= 2 && ctx->L < 192u &&
-                two_pass_blocks(ctx_planes(ctx), 1) <= kBandChunk * ctx->band_part_cap)
-                rc = sweep_two_pass(ctx, n, ser, ctx->band_part, 1);
-            else if (rc == ISING_OK) rc = sweep_bands(ctx, n, ser, ctx->band_part, kBandChunk, ctx->plan.rows, ctx->plan.cw);
+            if (rc == ISING_OK) rc = sweep_bands(ctx, n, ser, ctx->band_part, kBandChunk, ctx->plan.rows, ctx->plan.cw);
             break;
         default: return ISING_EUNSUPPORTED;
     }
