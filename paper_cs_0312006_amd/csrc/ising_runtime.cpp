@@ -19,6 +19,7 @@
 #include "ising.h"
 #include "ising_launch.hpp"
 #include "ising_creutz.hpp"
+#include "ising_creutz_pairs.hpp"
 #include "ising_hostcopy.hpp"
 #include "ising_runtime.hpp"
 
@@ -1394,9 +1395,8 @@ int ising_creutz_init(ising_ctx* ctx, const uint8_t* host, size_t n, uint8_t fil
     return ISING_OK;
 }
 
-// Buffers of the fused Creutz sweep: the second spin and demon buffers
-// (ping-pong) and per-tile partials for the (cw, rows) tiling.
-static int creutz_fused_prepare(ising_ctx* ctx, uint32_t cw, uint32_t rows) {
+// The second spin and demon buffers of the Creutz sweeps that ping-pong.
+static int creutz_second_buffers(ising_ctx* ctx) {
     const size_t N = (size_t)ctx->L * ctx->L;
     if (!ctx->buf[1]) {
         if (hipMalloc(&ctx->buf[1], N) != hipSuccess) {
@@ -1413,6 +1413,14 @@ static int creutz_fused_prepare(ising_ctx* ctx, uint32_t cw, uint32_t rows) {
             return ISING_ENOMEM;
         }
     }
+    return ISING_OK;
+}
+
+// Buffers of the fused Creutz sweep: the second spin and demon buffers and
+// per-tile partials for the (cw, rows) tiling.
+static int creutz_fused_prepare(ising_ctx* ctx, uint32_t cw, uint32_t rows) {
+    const int rc = creutz_second_buffers(ctx);
+    if (rc != ISING_OK) return rc;
     const uint32_t need = fused_tiles(ctx->L, cw, rows);
     if (need > ctx->cfpart_cap) {
         for (int k = 0; k < 2; ++k) {
@@ -1494,6 +1502,45 @@ static int creutz_sweep_bands(ising_ctx* ctx, uint64_t n, bool reverse, int64_t*
     return ISING_OK;
 }
 
+// The even part of n Creutz sweeps two a launch, for sides beyond the bands;
+// returns the sweeps left (all of them where this is not served: captured
+// streams, sides of partial words or beyond 32768, no room for the buffers).
+static int creutz_sweep_pairs(ising_ctx* ctx, uint64_t n, bool reverse, int64_t* ser, uint64_t* left) {
+    *left = n;
+    const uint32_t L = ctx->L;
+    if (n < 2 || row_bands_serve(L, band_count(L, band_default_rows(L)), true) || stream_capturing(ctx->stream))
+        return ISING_OK;
+    int cus = 0;
+    HIP_TRY(ctx, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device));
+    CreutzPairShape shape;
+    if (!creutz_pairs_shape(L, (uint32_t)cus, &shape)) return ISING_OK;
+    int rc = creutz_second_buffers(ctx);
+    if (rc == ISING_OK) rc = ctx_band_part(ctx, shape.bands);
+    if (rc == ISING_ENOMEM) return ISING_OK;
+    if (rc != ISING_OK) return rc;
+    const uint32_t f = reverse ? 1u : 0u;  // the colour of a sweep's first half
+    const uint64_t pairs = n / 2;
+    for (uint64_t done = 0; done < pairs;) {
+        const uint32_t m = (uint32_t)std::min<uint64_t>(pairs - done, kBandChunk / 2);
+        for (uint32_t k = 0; k < m; ++k) {
+            const Planes src = ctx_planes(ctx), dst = ctx_planes_alt(ctx);
+            const Planes ds = planes_of(ctx->demon, L), dd = planes_of(ctx->demon_alt, L);
+            CreutzPairArgs a{reinterpret_cast<const uint32_t*>(src.p[f]), reinterpret_cast<const uint32_t*>(src.p[f ^ 1u]),
+                             reinterpret_cast<const uint32_t*>(ds.p[f]), reinterpret_cast<const uint32_t*>(ds.p[f ^ 1u]),
+                             reinterpret_cast<uint32_t*>(dst.p[f]), reinterpret_cast<uint32_t*>(dst.p[f ^ 1u]),
+                             reinterpret_cast<uint32_t*>(dd.p[f]), reinterpret_cast<uint32_t*>(dd.p[f ^ 1u]),
+                             L, L / 8u, 0u, ctx->band_part + 4ull * k * shape.bands};
+            HIP_TRY(ctx, launch_creutz_pair(a, shape, reverse, ctx->stream));
+            ctx->cur ^= 1;
+            std::swap(ctx->demon, ctx->demon_alt);
+        }
+        HIP_TRY(ctx, launch_bands_reduce(ctx->band_part, shape.bands, 2u * m, ser + 4 * done, ctx->stream));
+        done += m;
+    }
+    *left = n - 2 * pairs;
+    return ISING_OK;
+}
+
 int ising_creutz_sweep(ising_ctx* ctx, uint64_t n, int reverse) {
     int rc = ctx_enter(ctx);
     if (rc != ISING_OK) return rc;
@@ -1510,6 +1557,13 @@ int ising_creutz_sweep(ising_ctx* ctx, uint64_t n, int reverse) {
         ctx->series_len += n;
         return ISING_OK;
     }
+    uint64_t left = n;
+    rc = creutz_sweep_pairs(ctx, n, reverse != 0, ser, &left);
+    if (rc != ISING_OK) return rc;
+    ctx->series_len += n - left;
+    ser += 2 * (n - left);
+    n = left;
+    if (n == 0) return ISING_OK;
     uint32_t cw = 0, rows = 0;
     if (!reverse && ctx->L % 8u == 0u && default_fused(ctx->L, &cw, &rows)) {
         rc = creutz_fused_prepare(ctx, cw, rows);
