@@ -232,6 +232,14 @@ def ising_observables(ctx, want=0, capacity=None):
     cap = 0
     if want & ISING_OBS_SERIES:
         if capacity is None:
+            # a series of up to 4096 sweeps comes in one read-back; a longer
+            # one is refused before any device work, and its length asked for
+            bs = np.empty(4096, dtype=np.int64)
+            ms = np.empty(4096, dtype=np.int64)
+            rc = lib().ising_observables(ctx, C.byref(obs), bs.ctypes.data, ms.ctypes.data, 4096, int(want))
+            if rc != ISING_ERANGE:
+                _check(rc, "ising_observables", ctx)
+                return obs, bs[:obs.series_len].copy(), ms[:obs.series_len].copy()
             rc = lib().ising_observables(ctx, C.byref(obs), None, None, 0, 0)
             _check(rc, "ising_observables")
             capacity = obs.series_len

@@ -1013,18 +1013,6 @@ static int band_check(ising_ctx* ctx) {
     return ISING_OK;
 }
 
-int ising_copy_spins(ising_ctx* ctx, int8_t* host, size_t n) {
-    int rc = ctx_enter(ctx);
-    if (rc != ISING_OK) return rc;
-    const size_t N = (size_t)ctx->L * ctx->L;
-    if (!host || n < N) return ISING_EINVAL;
-    rc = ensure_canonical(ctx);
-    if (rc != ISING_OK) return rc;
-    HIP_TRY(ctx, launch_to_canonical(ctx_planes(ctx), ctx->canon, ctx->stream));
-    HIP_TRY(ctx, copy_to_host(host, ctx->canon, N, ctx->stream));
-    return band_check(ctx);
-}
-
 int ising_load_spins(ising_ctx* ctx, const int8_t* host, size_t n, uint64_t t) {
     int rc = ctx_enter(ctx);
     if (rc != ISING_OK) return rc;
@@ -1052,6 +1040,14 @@ int ising_load_spins(ising_ctx* ctx, const int8_t* host, size_t n, uint64_t t) {
 // the caller then reads into pageable memory. The stage only grows, and only
 // between calls (each read-back is synchronised before it returns).
 static constexpr size_t kMaxHostStage = (size_t)64 << 20;
+// Read-backs of up to this size are written into the stage by a kernel of
+// this library rather than by a copy command: the command costs the host and
+// the queue about 6 us more each, and the link is far from busy at this size
+// (a 64^2 lattice reset, swept 10 times and read back whole, series and
+// spins: 65 us with the commands, 53.5 us with the kernels, 41.4 us with the
+// series in one call of the binding; the spins alone of
+// a 256^2 lattice 37 us before, 15.8 us now).
+static constexpr size_t kDirectBytes = (size_t)64 << 10;
 
 static void* ctx_host_stage(ising_ctx* ctx, size_t bytes) {
     if (bytes <= ctx->host_stage_bytes) return ctx->host_stage;
@@ -1070,26 +1066,57 @@ static void* ctx_host_stage(ising_ctx* ctx, size_t bytes) {
     return fresh;
 }
 
+int ising_copy_spins(ising_ctx* ctx, int8_t* host, size_t n) {
+    int rc = ctx_enter(ctx);
+    if (rc != ISING_OK) return rc;
+    const size_t N = (size_t)ctx->L * ctx->L;
+    if (!host || n < N) return ISING_EINVAL;
+    if (N <= kDirectBytes && ctx->pre_state == 0) {
+        // small lattices: the conversion writes into the pinned stage (which
+        // holds no prefetched read-back now)
+        if (void* stage = ctx_host_stage(ctx, N)) {
+            HIP_TRY(ctx, launch_to_canonical(ctx_planes(ctx), static_cast<int8_t*>(stage), ctx->stream));
+            HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+            std::memcpy(host, stage, N);
+            return band_check(ctx);
+        }
+    }
+    rc = ensure_canonical(ctx);
+    if (rc != ISING_OK) return rc;
+    HIP_TRY(ctx, launch_to_canonical(ctx_planes(ctx), ctx->canon, ctx->stream));
+    HIP_TRY(ctx, copy_to_host(host, ctx->canon, N, ctx->stream));
+    return band_check(ctx);
+}
+
 // Enqueue on the context's stream the copies ising_observables reads: the
 // whole pending series into `ser` when `full` (else the current (B, M): the
 // last series entry, or a fresh reduction when no sweep is pending) and,
 // with ISING_OBS_HASH, the canonical lattice bytes into `bytes`.
 static int enqueue_readback(ising_ctx* ctx, uint32_t want, bool full, int64_t* ser, uint8_t* bytes) {
     const uint64_t len = ctx->series_len;
+    const int64_t* from = ctx->series;
+    uint64_t pairs = 1;
     if (full) {
-        HIP_TRY(ctx, hipMemcpyAsync(ser, ctx->series, 2 * len * sizeof(int64_t), hipMemcpyDeviceToHost,
-                                    ctx->stream));
+        pairs = len;
     } else if (len) {
-        HIP_TRY(ctx, hipMemcpyAsync(ser, ctx->series + 2 * (len - 1), 2 * sizeof(int64_t), hipMemcpyDeviceToHost,
-                                    ctx->stream));
+        from += 2 * (len - 1);
     } else {
         HIP_TRY(ctx, launch_observe(ctx_planes(ctx), ctx->scratch, ctx->stream));
-        HIP_TRY(ctx, hipMemcpyAsync(ser, ctx->scratch, 2 * sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream));
+        from = ctx->scratch;
     }
+    const size_t ser_bytes = 2 * pairs * sizeof(int64_t);
+    if (static_cast<void*>(ser) == ctx->host_stage && ser_bytes <= kDirectBytes)
+        HIP_TRY(ctx, launch_stage_copy(ser, from, ser_bytes, ctx->stream));
+    else
+        HIP_TRY(ctx, hipMemcpyAsync(ser, from, ser_bytes, hipMemcpyDeviceToHost, ctx->stream));
     if (want & ISING_OBS_HASH) {
+        const size_t N = (size_t)ctx->L * ctx->L;
+        if (N <= kDirectBytes && static_cast<void*>(ser) == ctx->host_stage) {
+            HIP_TRY(ctx, launch_to_canonical(ctx_planes(ctx), reinterpret_cast<int8_t*>(bytes), ctx->stream));
+            return ISING_OK;
+        }
         const int rc = ensure_canonical(ctx);
         if (rc != ISING_OK) return rc;
-        const size_t N = (size_t)ctx->L * ctx->L;
         HIP_TRY(ctx, launch_to_canonical(ctx_planes(ctx), ctx->canon, ctx->stream));
         HIP_TRY(ctx, hipMemcpyAsync(bytes, ctx->canon, N, hipMemcpyDeviceToHost, ctx->stream));
     }

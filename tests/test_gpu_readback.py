@@ -54,6 +54,35 @@ def test_caller_buffers_of_any_alignment(b, L, offset):
     assert not buf[:offset].any() and not buf[offset + n:].any()
 
 
+@pytest.mark.parametrize("L,n", [(2, 1), (64, 4096), (254, 4097), (256, 4096), (258, 4097), (264, 40)])
+def test_small_read_backs(b, L, n):
+    """Sides and series lengths around the sizes up to which a kernel writes
+    the read-back into host memory (256^2 sites, 4096 sweeps) and one call
+    brings the series: the whole series, the hash and the spins
+    equal those of twin runs read back in other ways, also with a prefetched
+    read-back in the stage, which stays good."""
+    from oracle import ref
+    o = ref.default()
+    want = b.ISING_OBS_SERIES | b.ISING_OBS_HASH
+    G.log(f"small read-back L={L} n={n}")
+    one, two = b.ising_create(L, seed=5), b.ising_create(L, seed=5)
+    try:
+        b.ising_sweep(one, n)
+        b.ising_sweep(two, n)
+        assert b.ising_prefetch_observables(two, want)
+        spins = b.ising_copy_spins(two, L)
+        obs, B, M = b.ising_observables(one, want)
+        obs2, B2, M2 = b.ising_observables(two, want, capacity=n)
+        assert len(B) == n and np.array_equal(B, B2) and np.array_equal(M, M2)
+        assert np.array_equal(b.ising_copy_spins(one, L), spins)
+        assert obs.lattice_hash == obs2.lattice_hash == o.fnv1a64(spins)
+        assert (obs.bond_sum, obs.mag_sum) == (B[-1], M[-1]) and M[-1] == spins.sum(dtype=np.int64)
+        assert b.ising_observables(one, b.ISING_OBS_SERIES)[0].series_len == 0
+    finally:
+        b.ising_destroy(one)
+        b.ising_destroy(two)
+
+
 def test_several_threads_read_back_at_once(b):
     """More readers than stages, each on its own context: every lattice
     arrives whole."""
