@@ -20,6 +20,7 @@
 #include "ising_launch.hpp"
 #include "ising_creutz.hpp"
 #include "ising_creutz_pairs.hpp"
+#include "ising_tiles.hpp"
 #include "ising_hostcopy.hpp"
 #include "ising_runtime.hpp"
 
@@ -200,6 +201,29 @@ static uint32_t band_default_rows(uint32_t L) {
     return std::min<uint32_t>(rows > 11u && rows < 16u ? 16u : rows, std::max<uint32_t>(1u, L / 2u));
 }
 
+// The AUTO choice for a side that ising_tune has not timed.
+static bool untuned_plan(uint32_t L, Plan* out) {
+    if (L % 8u != 0u) return plan_for(L, ISING_PLAN_GENERIC, 0, 0, out);
+    if (L <= kResidentMaxL) return plan_for(L, ISING_PLAN_RESIDENT, 0, 0, out);
+    if (L >= kBandMinDefaultL && plan_for(L, ISING_PLAN_BANDS, 0, 0, out)) return true;
+    // Full rows where their bands are whole rounds of one workgroup of 16 waves
+    // a compute unit (32768^2, within 2% of the tiles either way), tiles
+    // elsewhere: us a sweep, rows against tiles, 18432^2 268 and 171, 24576^2
+    // 350 and 267, 28672^2 447 and 362.
+    Plan rows;
+    const bool have = plan_for(L, ISING_PLAN_FUSED_ROWS, 0, 0, &rows);
+    if (have && L / 8u == 16u * 64u * rows.cw && fused_rows_bands(L, rows.rows) % 256u == 0u) {
+        *out = rows;
+        return true;
+    }
+    if (plan_for(L, ISING_PLAN_FUSED, 0, 0, out)) return true;
+    if (have) {
+        *out = rows;
+        return true;
+    }
+    return plan_for(L, ISING_PLAN_TWO_PASS, 0, 0, out);
+}
+
 bool plan_for(uint32_t L, uint32_t kind, uint32_t cw, uint32_t rows, Plan* out) {
     Plan pl{};
     const bool words = (L % 8u) == 0u;
@@ -257,12 +281,7 @@ bool plan_for(uint32_t L, uint32_t kind, uint32_t cw, uint32_t rows, Plan* out) 
                     return true;
                 }
             }
-            if (!words) return plan_for(L, ISING_PLAN_GENERIC, 0, 0, out);
-            if (L <= kResidentMaxL) return plan_for(L, ISING_PLAN_RESIDENT, 0, 0, out);
-            if (L >= kBandMinDefaultL && plan_for(L, ISING_PLAN_BANDS, 0, 0, out)) return true;
-            if (plan_for(L, ISING_PLAN_FUSED_ROWS, 0, 0, out)) return true;
-            if (plan_for(L, ISING_PLAN_FUSED, 0, 0, out)) return true;
-            return plan_for(L, ISING_PLAN_TWO_PASS, 0, 0, out);
+            return untuned_plan(L, out);
         }
         default:
             return false;
@@ -408,6 +427,38 @@ static uint32_t generic_bands(const ising_ctx* ctx) {
     return row_bands_serve(ctx->L, G, false) ? G : 0;
 }
 
+// Partial sums of a sweep's tiles, bands or blocks: two buffers of at least
+// `need` pairs. On failure those there were stay.
+static int ctx_parts(ising_ctx* ctx, uint32_t need) {
+    if (need <= ctx->part_cap) return ISING_OK;
+    int64_t* fresh[2] = {nullptr, nullptr};
+    for (int k = 0; k < 2; ++k) {
+        if (hipMalloc(&fresh[k], (size_t)need * 2 * sizeof(int64_t)) != hipSuccess) {
+            (void)hipGetLastError();
+            if (k == 1) (void)hipFree(fresh[0]);
+            return ISING_ENOMEM;
+        }
+    }
+    for (int k = 0; k < 2; ++k) {
+        if (ctx->part[k]) (void)hipFree(ctx->part[k]);  // waits for the device
+        ctx->part[k] = fresh[k];
+    }
+    ctx->part_cap = need;
+    return ISING_OK;
+}
+
+// The second lattice buffer of sweeps that ping-pong under a plan with one.
+static int ctx_second_buffer(ising_ctx* ctx) {
+    if (ctx->buf[1]) return ISING_OK;
+    if (hipMalloc(&ctx->buf[1], (size_t)ctx->L * ctx->L) != hipSuccess) {
+        (void)hipGetLastError();
+        ctx->buf[1] = nullptr;
+        return ISING_ENOMEM;
+    }
+    ctx->owns_buf[1] = true;
+    return ISING_OK;
+}
+
 // Allocate what the context's plan needs: the second lattice buffer for
 // ping-pong, partial-sum buffers sized to the plan's tiles or blocks.
 int ctx_prepare_plan(ising_ctx* ctx) {
@@ -434,21 +485,7 @@ int ctx_prepare_plan(ising_ctx* ctx) {
     if (ctx->plan.kind == ISING_PLAN_FUSED) need = fused_tiles(ctx->L, ctx->plan.cw, ctx->plan.rows);
     if (ctx->plan.kind == ISING_PLAN_FUSED_ROWS) need = fused_rows_bands(ctx->L, ctx->plan.rows);
     if (ctx->plan.kind == ISING_PLAN_TWO_PASS) need = two_pass_blocks(pl, ctx->plan.cw);
-    if (need > ctx->part_cap) {
-        for (int k = 0; k < 2; ++k) {
-            if (ctx->part[k]) (void)hipFree(ctx->part[k]);
-            ctx->part[k] = nullptr;
-        }
-        ctx->part_cap = 0;
-        for (int k = 0; k < 2; ++k) {
-            if (hipMalloc(&ctx->part[k], (size_t)need * 2 * sizeof(int64_t)) != hipSuccess) {
-                (void)hipGetLastError();
-                return ISING_ENOMEM;
-            }
-        }
-        ctx->part_cap = need;
-    }
-    return ISING_OK;
+    return ctx_parts(ctx, need);
 }
 
 static size_t state_bytes_for(uint32_t L, const Plan& pl) {
@@ -788,6 +825,55 @@ int ising_reserve(ising_ctx* ctx, uint64_t sweeps) {
     return ctx_reserve_series(ctx, sweeps);
 }
 
+// Whether sweeps of this context run over wave tiles of any row length
+// (ising_tiles.hip). They do under the plan the side has by default (a plan
+// the caller set or tuned runs as it is) where that is slower; us a sweep,
+// default plan against tiles:
+//   the band plan in a field (general thresholds) beyond the row bands: 4104^2
+//     27.2 and 19.5, 8192^2 51.0 and 46.2, 16384^2 182 and 156. Without a field
+//     the bands by bits are faster: 4104^2 19.5 and 19.4, 8192^2 36.8 and 44,
+//     16384^2 137 and 157
+//   two passes beyond the bands (16384): 16392^2 216 and 177, 20000^2 264 and
+//     225, 32760^2 856 and 525; those of four words a lane just beyond are
+//     level (16416^2 170 and 172)
+static bool tiles_serve(const ising_ctx* ctx) {
+    const uint32_t L = ctx->L;
+    if (L % 8u != 0u || L <= 4096u) return false;
+    if (ctx->plan.kind == ISING_PLAN_BANDS) {
+        if (bits_mode(ctx->table) != 3u || row_bands_serve(L, band_count(L, ctx->plan.rows), false)) return false;
+    } else if (ctx->plan.kind != ISING_PLAN_TWO_PASS || band_words(L) <= kBandMaxWr) {
+        return false;
+    }
+    Plan d;
+    return untuned_plan(L, &d) && d.kind == ctx->plan.kind && d.cw == ctx->plan.cw && d.rows == ctx->plan.rows;
+}
+
+// n sweeps over tiles; *served says whether they were (not on captured
+// streams, nor without room for the second buffer).
+static int sweep_tiles(ising_ctx* ctx, uint64_t n, int64_t* ser, bool* served) {
+    *served = false;
+    TileShape shape;
+    if (!tiles_serve(ctx) || stream_capturing(ctx->stream) || !tiles_shape(ctx->L, &shape)) return ISING_OK;
+    int rc = ctx_second_buffer(ctx);
+    if (rc == ISING_OK) rc = ctx_parts(ctx, shape.tiles);
+    if (rc != ISING_OK) return rc == ISING_ENOMEM ? ISING_OK : rc;
+    for (uint64_t k = 0; k < n; ++k) {
+        const Planes src = ctx_planes(ctx), dst = ctx_planes_alt(ctx);
+        const FusedArgs a{reinterpret_cast<const uint32_t*>(src.p[0]), reinterpret_cast<const uint32_t*>(src.p[1]),
+                          reinterpret_cast<uint32_t*>(dst.p[0]), reinterpret_cast<uint32_t*>(dst.p[1]),
+                          ctx->L, ctx->L / 8u, (uint32_t)(ctx->t + k), (uint32_t)ctx->p.seed,
+                          (uint32_t)(ctx->p.seed >> 32), shape.n_tx, shape.tiles, ctx->part[k & 1]};
+        PartialReduce red{nullptr, 0, nullptr};
+        if (k > 0) red = PartialReduce{ctx->part[(k - 1) & 1], shape.tiles, ser + 2 * (k - 1)};
+        HIP_TRY(ctx, launch_tiles(a, ctx->table, shape, red, ctx->stream));
+        ctx->cur ^= 1;
+    }
+    HIP_TRY(ctx, launch_reduce_partials(PartialReduce{ctx->part[(n - 1) & 1], shape.tiles, ser + 2 * (n - 1)},
+                                        ctx->stream));
+    *served = true;
+    return ISING_OK;
+}
+
 int ising_sweep(ising_ctx* ctx, uint64_t n) {
     int rc = ctx_enter(ctx);
     if (rc != ISING_OK) return rc;
@@ -804,6 +890,14 @@ int ising_sweep(ising_ctx* ctx, uint64_t n) {
         fill_batch_item(ctx, n, false, it);
         if (bits_fit(ctx->L) && !bytes_fit(ctx->L)) it.bits = bits_mode(ctx->table);
         HIP_TRY(ctx, launch_batch_one(it, ctx->stream));
+        ctx->t += n;
+        ctx->series_len += n;
+        return ISING_OK;
+    }
+    bool served = false;
+    rc = sweep_tiles(ctx, n, ctx->series + 2 * ctx->series_len, &served);
+    if (rc != ISING_OK) return rc;
+    if (served) {
         ctx->t += n;
         ctx->series_len += n;
         return ISING_OK;
@@ -1425,14 +1519,8 @@ int ising_creutz_init(ising_ctx* ctx, const uint8_t* host, size_t n, uint8_t fil
 // The second spin and demon buffers of the Creutz sweeps that ping-pong.
 static int creutz_second_buffers(ising_ctx* ctx) {
     const size_t N = (size_t)ctx->L * ctx->L;
-    if (!ctx->buf[1]) {
-        if (hipMalloc(&ctx->buf[1], N) != hipSuccess) {
-            (void)hipGetLastError();
-            ctx->buf[1] = nullptr;
-            return ISING_ENOMEM;
-        }
-        ctx->owns_buf[1] = true;
-    }
+    const int rc = ctx_second_buffer(ctx);
+    if (rc != ISING_OK) return rc;
     if (!ctx->demon_alt) {
         if (hipMalloc(&ctx->demon_alt, N) != hipSuccess) {
             (void)hipGetLastError();
