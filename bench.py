@@ -48,21 +48,21 @@ PROFILED = {
 }
 
 
-# Creutz: the fused sweep at 32768^2 (profiles/k_creutz_fused_creutz_32768.md,
-# mean of 22 dispatches)
-PROFILED_CREUTZ_SOURCES = "6787c46f73def973"
-PROFILED_CREUTZ = {"kernel": "k_creutz_fused<4,32>",
-                   "hbm_bytes_per_sweep": (1246597.4 * 2.0 + 2097426.2) * 1024}
+# Creutz: two sweeps a launch at 32768^2 (profiles/k_creutz_fused_creutz_32768.md,
+# mean of 11 dispatches)
+PROFILED_CREUTZ_SOURCES = "77870df3a3a2e4fa"
+PROFILED_CREUTZ = {"kernel": "k_creutz_pairs<4>",
+                   "hbm_bytes_per_sweep": (1120148.7 * 2.0 + 2097526.4) * 1024 / 2}
 
 # Batched configuration (1024 lattices): the resident kernel the tuned AUTO
 # plan runs (profiles/k_batch_bits_batched_1024.md, one dispatch of 2000
 # sweeps) and the stepped plan's fused walk (profiles/k_multi_fused_batched_1024.md,
 # mean of 160 dispatches, 16-row tiles)
 BATCH_FILES = ("ising_batch.hip", "ising_bits.hpp", "ising_device.hpp", "ising_launch.hpp")
-PROFILED_BATCH_SOURCES = "e86f8f0d0ff597dc"
+PROFILED_BATCH_SOURCES = "4b2ac64d3ef3a188"
 PROFILED_BATCH = {"kernel": "k_batch (bit-packed lattices in workgroup memory)",
-                  "valu_lane_ops_per_attempt": 192905902547.0 * 64 / (388630784 * 2000),
-                  "valu_busy_rocprof": 0.932}
+                  "valu_lane_ops_per_attempt": 192747224258.0 * 64 / (388630784 * 2000),
+                  "valu_busy_rocprof": 0.934}
 MULTI_FUSED_FILES = ("ising_multi_fused.hip", "ising_fused_core.hpp", "ising_device.hpp", "ising_launch.hpp")
 PROFILED_MULTI_FUSED_SOURCES = "562f1a3a50200cd3"
 PROFILED_MULTI_FUSED = {"kernel": "k_multi_fused (one launch per sweep)",
@@ -112,7 +112,8 @@ def kernel_sources_hash(files=HEADLINE_FILES):
     return h.hexdigest()[:16]
 
 
-CREUTZ_FILES = ("ising_creutz_fused.hip", "ising_creutz.hpp", "ising_device.hpp", "ising_launch.hpp")
+CREUTZ_FILES = ("ising_creutz_pairs.hip", "ising_creutz_pairs.hpp", "ising_creutz.hpp", "ising_device.hpp",
+                "ising_fused_core.hpp")
 
 
 def progress(msg):
@@ -456,7 +457,7 @@ def run_creutz(b, torch, stream, sweeps, metropolis_value, cpu=True):
         b.ising_destroy(ctx)
     N = run.L * run.L
     value = N * sweeps / ms / 1e6
-    achieved = 4.0 * N / (ms / sweeps * 1e-3) / 1e9
+    achieved = 2.0 * N / (ms / sweeps * 1e-3) / 1e9
     same = kernel_sources_hash(CREUTZ_FILES) == PROFILED_CREUTZ_SOURCES
     traffic = PROFILED_CREUTZ["hbm_bytes_per_sweep"] / (ms / sweeps * 1e-3) / 1e9 if same else None
     t_demon = 4.0 / __import__("math").log1p(N / demons) if demons else None
@@ -486,8 +487,8 @@ def run_creutz(b, torch, stream, sweeps, metropolis_value, cpu=True):
             "demon_temperature": t_demon,
             "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                         "kernel": PROFILED_CREUTZ["kernel"] + " (one launch per sweep)",
-                         "algorithmic_bytes_per_sweep": 4.0 * N}}
+                         "kernel": PROFILED_CREUTZ["kernel"] + " (two sweeps a launch)",
+                         "algorithmic_bytes_per_sweep": 2.0 * N}}
 
 
 def run_percolation(b, cpu=True, spanning=True):

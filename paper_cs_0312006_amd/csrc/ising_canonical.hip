@@ -5,7 +5,7 @@
 // the bytes of plane i & 1 (even columns) and of the other plane (odd
 // columns) in turn: two byte permutes a word pair. Bound by memory (each byte
 // read and written once): with four words of each plane a thread, 16384^2
-// takes 0.13 ms and 32768^2 0.50 ms (4.3 TB/s), against 0.54 and 2.03 ms with
+// takes 0.09 ms and 32768^2 0.46 ms (4.6 TB/s), against 0.54 and 2.03 ms with
 // a thread a site (a 64-bit division and a byte load and store each). The
 // site kernels stay for sides of partial words and for buffers that are not
 // aligned for the wider accesses.
