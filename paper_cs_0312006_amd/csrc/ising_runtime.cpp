@@ -718,6 +718,10 @@ static int create_common(const ising_params* params, void* dev_buf, size_t bytes
     ctx->p = *params;
     ctx->L = params->L;
     ctx->plan = plan;
+    if ((params->flags & 0xffu) == ISING_PLAN_AUTO) {
+        std::lock_guard<std::mutex> g(g_tuned_mu);
+        ctx->plan_by_side = g_tuned.find(params->L) == g_tuned.end();
+    }
     build_accept_table(params->J, params->h, params->T, &ctx->table, &ctx->exact);
     hostcopy_retain();
     if (hipGetDevice(&ctx->device) != hipSuccess) {
@@ -817,9 +821,10 @@ int ising_reserve(ising_ctx* ctx, uint64_t sweeps) {
 }
 
 // Whether sweeps of this context run over wave tiles of any row length
-// (ising_tiles.hip). They do under the plan the side has by default (a plan
-// the caller set or tuned runs as it is) where that is slower; us a sweep,
-// default plan against tiles:
+// (ising_tiles.hip). They do under the plan the side has by default (any
+// other plan that the caller sets or tunes runs as it is; ising_tune times
+// the default with its tiles) where that is slower; us a sweep, default plan
+// against tiles:
 //   the band plan in a field (general thresholds) beyond the row bands: 4104^2
 //     27.2 and 19.5, 8192^2 51.0 and 46.2, 16384^2 182 and 156. Without a field
 //     the bands by bits are faster: 4104^2 19.5 and 19.4, 8192^2 36.8 and 44,
@@ -839,15 +844,28 @@ static bool tiles_serve(const ising_ctx* ctx) {
     return untuned_plan(L, &d) && d.kind == ctx->plan.kind && d.cw == ctx->plan.cw && d.rows == ctx->plan.rows;
 }
 
-// n sweeps over tiles; *served says whether they were (not on captured
-// streams, nor without room for the second buffer).
+// Sweeps under a plan in place leave the lattice in the buffer they found it
+// in: graphs that a caller captured hold its address. (A copy costs about a
+// sweep.)
+static int ctx_to_buffer(ising_ctx* ctx, int home) {
+    if (ctx->cur == home) return ISING_OK;
+    HIP_TRY(ctx, hipMemcpyAsync(ctx->buf[home], ctx->buf[ctx->cur], (size_t)ctx->L * ctx->L, hipMemcpyDeviceToDevice,
+                                ctx->stream));
+    ctx->cur = home;
+    return ISING_OK;
+}
+
+// n sweeps over tiles; *served says whether they were (not one alone, which
+// with the copy back takes longer than in place, 20000^2 390 us against 270;
+// not on captured streams, nor without room for the second buffer).
 static int sweep_tiles(ising_ctx* ctx, uint64_t n, int64_t* ser, bool* served) {
     *served = false;
     TileShape shape;
-    if (!tiles_serve(ctx) || stream_capturing(ctx->stream) || !tiles_shape(ctx->L, &shape)) return ISING_OK;
+    if (n < 2 || !tiles_serve(ctx) || stream_capturing(ctx->stream) || !tiles_shape(ctx->L, &shape)) return ISING_OK;
     int rc = ctx_second_buffer(ctx);
     if (rc == ISING_OK) rc = ctx_parts(ctx, shape.tiles);
     if (rc != ISING_OK) return rc == ISING_ENOMEM ? ISING_OK : rc;
+    const int home = ctx->cur;
     for (uint64_t k = 0; k < n; ++k) {
         const Planes src = ctx_planes(ctx), dst = ctx_planes_alt(ctx);
         const FusedArgs a{reinterpret_cast<const uint32_t*>(src.p[0]), reinterpret_cast<const uint32_t*>(src.p[1]),
@@ -862,19 +880,32 @@ static int sweep_tiles(ising_ctx* ctx, uint64_t n, int64_t* ser, bool* served) {
     HIP_TRY(ctx, launch_reduce_partials(PartialReduce{ctx->part[(n - 1) & 1], shape.tiles, ser + 2 * (n - 1)},
                                         ctx->stream));
     *served = true;
-    return ISING_OK;
+    return ctx_to_buffer(ctx, home);
 }
+
+// A captured stream, or a caller of ising_sweep_static with several contexts
+// in flight, cannot use a band launch (its tags advance on the host; its
+// partials go to the array that calls share). The smallest sides that run
+// bands by default were served there by plans without those limits, and are
+// by one workgroup.
+static bool one_workgroup(const ising_ctx* ctx, uint32_t limit) {
+    return ctx->plan.kind == ISING_PLAN_BANDS && ctx->plan_by_side && ctx->L <= limit;
+}
+constexpr uint32_t kCaptureMaxL = 184;    // ising_sweep under capture, and static sweeps
+constexpr uint32_t kNoScratchMaxL = 128;  // static sweeps that use no shared array
 
 int ising_sweep(ising_ctx* ctx, uint64_t n) {
     int rc = ctx_enter(ctx);
     if (rc != ISING_OK) return rc;
     if (n == 0) return ISING_OK;
-    if (ctx->plan.kind == ISING_PLAN_BANDS && stream_capturing(ctx->stream)) return ISING_EUNSUPPORTED;
+    const bool captured = ctx->plan.kind == ISING_PLAN_BANDS && stream_capturing(ctx->stream);
+    if (captured && !one_workgroup(ctx, kCaptureMaxL)) return ISING_EUNSUPPORTED;
     if (ctx->t + n > ((uint64_t)1 << 32)) return ISING_ERANGE;
     rc = ctx_reserve_series(ctx, n);
     if (rc != ISING_OK) return rc;
     ++ctx->gen;
-    if (ctx->plan.kind == ISING_PLAN_RESIDENT || (ctx->plan.kind == ISING_PLAN_BANDS && short_band_call(ctx->L, n))) {
+    if (ctx->plan.kind == ISING_PLAN_RESIDENT ||
+        (ctx->plan.kind == ISING_PLAN_BANDS && (captured || short_band_call(ctx->L, n)))) {
         // one workgroup runs every sweep from local memory (bytes: a lone
         // lattice's latency, not the chip's throughput, sets the time)
         BatchItem it;
@@ -949,7 +980,8 @@ int ising_sweep_static(ising_ctx* ctx, uint64_t n, int64_t* series_dev) {
     if (ctx->plan.kind == ISING_PLAN_TWO_PASS) pairs = two_pass_blocks(ctx_planes(ctx), ctx->plan.cw);
     // under capture the band plan's sweeps run as two-pass launches
     const bool bands_as_two_pass = ctx->plan.kind == ISING_PLAN_BANDS && stream_capturing(ctx->stream);
-    if (ctx->plan.kind == ISING_PLAN_BANDS)
+    const bool one_group = one_workgroup(ctx, bands_as_two_pass ? kCaptureMaxL : kNoScratchMaxL);
+    if (ctx->plan.kind == ISING_PLAN_BANDS && !one_group)
         pairs = bands_as_two_pass ? two_pass_blocks(ctx_planes(ctx), 1) : band_count(ctx->L, ctx->plan.rows);
     if (pairs > ISING_STATIC_SCRATCH_PAIRS) return ISING_ERANGE;
     int64_t* sc = nullptr;
@@ -958,7 +990,7 @@ int ising_sweep_static(ising_ctx* ctx, uint64_t n, int64_t* series_dev) {
         if (!sc) return ctx_fail(ctx, hipErrorInvalidSymbol, "hipGetSymbolAddress(scratch)");
     }
     ++ctx->gen;
-    switch (ctx->plan.kind) {
+    switch (one_group ? ISING_PLAN_RESIDENT : ctx->plan.kind) {
         case ISING_PLAN_FUSED:
         case ISING_PLAN_FUSED_ROWS: {
             const uint32_t tiles = pairs / 2;
@@ -1358,6 +1390,7 @@ int ising_plan_set(ising_ctx* ctx, uint32_t plan, uint32_t cw, uint32_t rows) {
     ctx->plan = pl;
     rc = ctx_prepare_plan(ctx);
     if (rc != ISING_OK) ctx->plan = old;
+    else ctx->plan_by_side = false;
     return rc;
 }
 
@@ -1468,6 +1501,7 @@ int ising_tune(ising_ctx* ctx, uint32_t trial_sweeps) {
         ctx->plan = old;
         return rc;
     }
+    ctx->plan_by_side = false;
     std::lock_guard<std::mutex> g(g_tuned_mu);
     g_tuned[L] = best;
     return ISING_OK;
@@ -1626,6 +1660,7 @@ static int creutz_sweep_pairs(ising_ctx* ctx, uint64_t n, bool reverse, int64_t*
     if (rc != ISING_OK) return rc;
     const uint32_t f = reverse ? 1u : 0u;  // the colour of a sweep's first half
     const uint64_t pairs = n / 2;
+    const int home = ctx->cur;
     for (uint64_t done = 0; done < pairs;) {
         const uint32_t m = (uint32_t)std::min<uint64_t>(pairs - done, kBandChunk / 2);
         for (uint32_t k = 0; k < m; ++k) {
@@ -1644,7 +1679,9 @@ static int creutz_sweep_pairs(ising_ctx* ctx, uint64_t n, bool reverse, int64_t*
         done += m;
     }
     *left = n - 2 * pairs;
-    return ISING_OK;
+    // as in place, where single sweeps are
+    uint32_t cw = 0, rows = 0;
+    return reverse || !default_fused(L, &cw, &rows) ? ctx_to_buffer(ctx, home) : ISING_OK;
 }
 
 int ising_creutz_sweep(ising_ctx* ctx, uint64_t n, int reverse) {

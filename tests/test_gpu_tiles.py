@@ -55,3 +55,82 @@ def test_tiles_match_the_per_site_plan_and_the_oracle(b, L, J, h, T, calls):
         win, valid = o.window_run(L, J, h, T, p["seed"], 0, n, i0, j0, win)
         got = s[np.ix_((np.arange(wide) + i0) % L, (np.arange(wide) + j0) % L)]
         assert valid.any() and np.array_equal(got[valid], win[valid])
+
+
+@pytest.mark.parametrize("L,h,creutz", [(4104, 0.1, False), (4104, 0.0, True)])
+def test_captured_sweeps_stay_valid(b, L, h, creutz):
+    """A graph of static sweeps holds the lattice's address: odd tile sweeps
+    and reversed Creutz pairs leave the lattice where it was."""
+    import torch
+    G.log(f"graph after eager sweeps L={L} creutz={creutz}")
+    s, n = torch.cuda.Stream(), 2
+    p = dict(J=1.0, h=h, T=2.3, seed=9)
+    c, r = b.ising_create(L, stream=s.cuda_stream, **p), b.ising_create(L, **p)
+    try:
+        if creutz:
+            b.ising_creutz_init(c, None, 3)
+        start = b.ising_copy_spins(c, L)
+        series = torch.zeros(2 * n, dtype=torch.int64, device="cuda")
+        b.ising_sweep_static(c, n, series.data_ptr())
+        b.ising_load_spins(c, start, 0)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            b.ising_sweep_static(c, n, series.data_ptr())
+        b.ising_sweep(r, n)
+        _, B, M = b.ising_observables(r, b.ISING_OBS_SERIES)
+        for _ in range(3):
+            if creutz:
+                b.ising_creutz_sweep(c, 2, reverse=True)
+            else:
+                b.ising_sweep(c, 5)
+            b.ising_load_spins(c, start, 0)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            got = series.cpu().numpy()
+            assert np.array_equal(got[0::2], B) and np.array_equal(got[1::2], M)
+            assert np.array_equal(b.ising_copy_spins(c, L), b.ising_copy_spins(r, L))
+    finally:
+        b.ising_destroy(c)
+        b.ising_destroy(r)
+
+
+@pytest.mark.parametrize("L", [96, 128, 136, 184])
+def test_small_default_sides_are_captured_in_one_workgroup(b, L):
+    """ising_sweep and ising_sweep_static of a default context of these sides
+    can be captured; every replay equals the eager run."""
+    import torch
+    G.log(f"captured sweeps of a small default side L={L}")
+    s, n = torch.cuda.Stream(), 6
+    c, r = b.ising_create(L, h=0.05, T=2.3, seed=L, stream=s.cuda_stream), b.ising_create(L, h=0.05, T=2.3, seed=L)
+    try:
+        start = b.ising_copy_spins(c, L)
+        b.ising_reserve(c, 64)
+        series = torch.zeros(2 * n, dtype=torch.int64, device="cuda")
+        b.ising_sweep_static(c, n, series.data_ptr())
+        b.ising_load_spins(c, start, 0)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            b.ising_sweep_static(c, n, series.data_ptr())
+            b.ising_sweep(c, n)
+        b.ising_sweep(r, 2 * n)
+        _, B, M = b.ising_observables(r, b.ISING_OBS_SERIES)
+        for _ in range(3):
+            b.ising_load_spins(c, start, 0)
+            series.fill_(-7)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            got = series.cpu().numpy()
+            assert np.array_equal(got[0::2], B[:n]) and np.array_equal(got[1::2], M[:n])
+            assert np.array_equal(b.ising_copy_spins(c, L), b.ising_copy_spins(r, L))
+        b.ising_plan_set(c, b.ISING_PLAN_BANDS)
+        with torch.cuda.graph(torch.cuda.CUDAGraph(), stream=s):
+            with pytest.raises(b.IsingError):
+                b.ising_sweep(c, 1)
+            b.ising_sweep_static(c, 1, series.data_ptr())
+    finally:
+        b.ising_destroy(c)
+        b.ising_destroy(r)
