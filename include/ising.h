@@ -65,10 +65,12 @@ extern "C" {
 /* Plan selection (ising_params.flags, low byte). AUTO picks per lattice side:
  * the workgroup-resident kernel for small sides, the band-resident plan for
  * sides 96 to 16384 (about one band of rows per compute unit), the fused
- * one-pass sweep by full-row workgroups where a row fits one workgroup, the
- * fused sweep by wave tiles for larger sides, the two-pass in-place sweep
- * otherwise. The others force a path (ISING_EUNSUPPORTED if the side does
- * not fit it). */
+ * one-pass sweep by wave tiles for larger sides whose rows are whole tiles,
+ * the two-pass plan otherwise. Under those defaults, lattices in a field
+ * beyond 4096 and sides of the two-pass plan beyond 16384 are swept in one
+ * pass between their buffer and a second one, allocated at the first sweep
+ * (not under stream capture, nor where it does not fit). The others force a
+ * path (ISING_EUNSUPPORTED if the side does not fit it). */
 #define ISING_PLAN_AUTO 0u
 #define ISING_PLAN_TWO_PASS 1u  /* one launch per colour, in place */
 #define ISING_PLAN_FUSED 2u     /* one launch per sweep, ping-pong buffers; a wave per tile */
@@ -242,8 +244,8 @@ int ising_sweep_batch(ising_ctx* const* ctxs, const uint64_t* n_sweeps, size_t c
  *   of side up to 1072 is held in the workgroup's local memory at one bit
  *   per site for all its sweeps, except that lattices of side up to 256 are
  *   held as bytes when h != 0 or while the batch has fewer lattices than
- *   the launch has workgroups (lower latency per sweep); larger ones are
- *   swept in global memory;
+ *   the launch has workgroups (lower latency per sweep; up to 176 in
+ *   registers); larger ones are swept in global memory;
  *   (a single context's ising_sweep under the resident plan runs the same
  *   per-lattice code in one workgroup, launched directly);
  * ISING_BATCH_STEPPED: every sweep is one launch over the tiles of all
