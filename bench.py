@@ -33,24 +33,24 @@ VALU_PEAK_LANE_OPS = 256 * 64 * 2.4e9  # 256 CUs x 64 lanes x 2.4 GHz (32-bit op
 # copy in the same runs reads 524300 KiB of FETCH_SIZE and writes 1048576
 # KiB of WRITE_SIZE. VALU lane-ops are SQ_INSTS_VALU x 64; VALU busy is
 # SQ_ACTIVE_INST_VALU / 256 compute units / (GRBM_GUI_ACTIVE / 8 XCDs).
-PROFILED_SOURCES = "aaf5cc389756ada4"
+PROFILED_SOURCES = "6c1853b598a1f2f2"
 PROFILED = {
-    # profiles/k_fused_rows_ising2d_32768.md: FETCH/WRITE means of 140
-    # dispatches, VALU counters of the 35 in the counter pass
-    "k_fused_rows<4,128>": {"hbm_bytes_per_launch": (532789.7 * 2.0 + 1048621.0) * 1024,
-                            "valu_lane_ops_per_attempt": 231620842.4 * 64 / 2 ** 30,
-                            "valu_busy_rocprof": 0.845},
-    # the wave-tile shape the autotuner takes when it beats the full rows by
-    # more than its margin (same passes: 27 dispatches for bytes, 132 for VALU)
-    "k_fused<4,32>": {"hbm_bytes_per_launch": (647856.8 * 2.0 + 1048835.0) * 1024,
-                      "valu_lane_ops_per_attempt": 227870305.6 * 64 / 2 ** 30,
-                      "valu_busy_rocprof": 0.842},
+    # profiles/k_fused_ising2d_32768.md: means of 140 dispatches
+    "k_fused<4,32>": {"hbm_bytes_per_launch": (645467.9 * 2.0 + 1048834.7) * 1024,
+                      "valu_lane_ops_per_attempt": 227870299.2 * 64 / 2 ** 30,
+                      "valu_busy_rocprof": 0.840},
+    # profiles/k_fused_rows_ising2d_32768.md: the shape the autotuner takes
+    # when it beats the tiles by more than its margin (same passes, 27
+    # dispatches)
+    "k_fused_rows<4,128>": {"hbm_bytes_per_launch": (533306.9 * 2.0 + 1048629.0) * 1024,
+                            "valu_lane_ops_per_attempt": 231620814.6 * 64 / 2 ** 30,
+                            "valu_busy_rocprof": 0.847},
 }
 
 
 # Creutz: two sweeps a launch at 32768^2 (profiles/k_creutz_fused_creutz_32768.md,
 # mean of 11 dispatches)
-PROFILED_CREUTZ_SOURCES = "77870df3a3a2e4fa"
+PROFILED_CREUTZ_SOURCES = "79c936fd12d4dad2"
 PROFILED_CREUTZ = {"kernel": "k_creutz_pairs<4>",
                    "hbm_bytes_per_sweep": (1120148.7 * 2.0 + 2097526.4) * 1024 / 2}
 
@@ -59,16 +59,16 @@ PROFILED_CREUTZ = {"kernel": "k_creutz_pairs<4>",
 # sweeps) and the stepped plan's fused walk (profiles/k_multi_fused_batched_1024.md,
 # mean of 160 dispatches, 16-row tiles)
 BATCH_FILES = ("ising_batch.hip", "ising_bits.hpp", "ising_device.hpp", "ising_launch.hpp")
-PROFILED_BATCH_SOURCES = "4b2ac64d3ef3a188"
+PROFILED_BATCH_SOURCES = "3b566fa8596fe164"
 PROFILED_BATCH = {"kernel": "k_batch (bit-packed lattices in workgroup memory)",
                   "valu_lane_ops_per_attempt": 192747224258.0 * 64 / (388630784 * 2000),
                   "valu_busy_rocprof": 0.934}
 MULTI_FUSED_FILES = ("ising_multi_fused.hip", "ising_fused_core.hpp", "ising_device.hpp", "ising_launch.hpp")
-PROFILED_MULTI_FUSED_SOURCES = "562f1a3a50200cd3"
+PROFILED_MULTI_FUSED_SOURCES = "d149c70c430dab77"
 PROFILED_MULTI_FUSED = {"kernel": "k_multi_fused (one launch per sweep)",
                         "valu_lane_ops_per_attempt": 131454301.0 * 64 / 388630784,
-                        "valu_busy_rocprof": 0.887,
-                        "hbm_bytes_per_sweep": (244661.1 * 2.0 + 412989.1) * 1024}
+                        "valu_busy_rocprof": 0.881,
+                        "hbm_bytes_per_sweep": (244553.9 * 2.0 + 412847.0) * 1024}
 
 
 def batched_roofline(res, stepped):

@@ -67,8 +67,8 @@ struct Engine {
     hipGraphExec_t mexec = nullptr;
     uint32_t mgrid = 0;
     // stepped plan, fused walk (sides multiple of 16)
-    hipGraph_t fgraph = nullptr;
-    hipGraphExec_t fexec = nullptr;
+    hipGraph_t fgraph[2] = {};  // rows streamed; rows found in cache
+    hipGraphExec_t fexec[2] = {};
     uint32_t fslots = 0;  // waves of the fused walk resident on the GPU at once
     uint32_t fgrid = 0;   // workgroups per launch of the fused walk
     int64_t* d_part = nullptr;  // (B, M) of every tile / virtual block for each sweep of a replay
@@ -89,10 +89,12 @@ void release_buffers(Engine& e) {
     if (e.mgraph) (void)hipGraphDestroy(e.mgraph);
     e.mexec = nullptr;
     e.mgraph = nullptr;
-    if (e.fexec) (void)hipGraphExecDestroy(e.fexec);
-    if (e.fgraph) (void)hipGraphDestroy(e.fgraph);
-    e.fexec = nullptr;
-    e.fgraph = nullptr;
+    for (int k = 0; k < 2; ++k) {
+        if (e.fexec[k]) (void)hipGraphExecDestroy(e.fexec[k]);
+        if (e.fgraph[k]) (void)hipGraphDestroy(e.fgraph[k]);
+        e.fexec[k] = nullptr;
+        e.fgraph[k] = nullptr;
+    }
     if (e.d_stage) (void)hipFree(e.d_stage);
     if (e.h_stage) (void)hipHostFree(e.h_stage);
     e.d_stage = nullptr;
@@ -241,18 +243,18 @@ hipError_t ensure_partials(Engine& e, uint64_t tiles) {
 
 // Capture G sweeps of the stepped plan's fused walk (one advance node, G
 // launches, one reduce of the tile partials into the series).
-hipError_t ensure_fused_graph(Engine& e) {
-    if (e.fexec) return hipSuccess;
+hipError_t ensure_fused_graph(Engine& e, bool cached) {
+    if (e.fexec[cached]) return hipSuccess;
     hipStream_t cap = nullptr;
     hipError_t r = hipStreamCreateWithFlags(&cap, hipStreamNonBlocking);
     if (r != hipSuccess) return r;
     r = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
     if (r == hipSuccess) {
-        hipError_t lr = launch_multi_fused_graph_body(e.d_items, e.d_vbs, e.d_mhdr, kSweepsPerReplay, e.fgrid, cap);
-        r = hipStreamEndCapture(cap, &e.fgraph);
+        hipError_t lr = launch_multi_fused_graph_body(e.d_items, e.d_vbs, e.d_mhdr, kSweepsPerReplay, e.fgrid, cached, cap);
+        r = hipStreamEndCapture(cap, &e.fgraph[cached]);
         if (lr != hipSuccess) r = lr;
     }
-    if (r == hipSuccess) r = hipGraphInstantiate(&e.fexec, e.fgraph, nullptr, nullptr, 0);
+    if (r == hipSuccess) r = hipGraphInstantiate(&e.fexec[cached], e.fgraph[cached], nullptr, nullptr, 0);
     (void)hipStreamDestroy(cap);
     return r;
 }
@@ -443,9 +445,13 @@ int engine_run(ising_ctx* const* ctxs, const uint64_t* n, size_t count, hipStrea
         r = ensure_graph(e, s);
         if (r == hipSuccess) r = hipGraphLaunch(e.exec, s);
     } else if (fused) {
-        r = ensure_fused_graph(e);
+        uint64_t sites = 0;
+        for (size_t k = 0; k < count; ++k)
+            if (n[k]) sites += (uint64_t)ctxs[k]->L * ctxs[k]->L;
+        const bool cached = rows_stay_cached(sites);
+        r = ensure_fused_graph(e, cached);
         const uint64_t replays = (max_n + kSweepsPerReplay - 1) / kSweepsPerReplay;
-        for (uint64_t k = 0; r == hipSuccess && k < replays; ++k) r = hipGraphLaunch(e.fexec, s);
+        for (uint64_t k = 0; r == hipSuccess && k < replays; ++k) r = hipGraphLaunch(e.fexec[cached], s);
     } else {
         r = ensure_multi_graph(e);
         const uint64_t replays = (max_n + kSweepsPerReplay - 1) / kSweepsPerReplay;

@@ -50,21 +50,25 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc(const uint32_t* p) 
 // gfx950's buffer instructions). A sweep reads every row once and writes it
 // once, and the planes of any lattice this walk streams are far larger than
 // the caches; with the hint the 32768^2 sweep measured 2-5% faster (wave
-// tiles and full rows), the stepped batch walk unchanged.
+// tiles and full rows).
 constexpr int kRowCachePolicy = 2;
+// Where both buffers of all lattices in flight fit the 256 MB cache, a sweep
+// finds there what the last one wrote, unless it was written with the hint
+// (rows_stay_cached).
+constexpr int kRowCachePlain = 0;
 
 // CW words at byte offset xb (lane) + soff (row, uniform) of a plane.
-template <int CW>
+template <int CW, int POLICY = kRowCachePolicy>
 __device__ __forceinline__ Row<CW> ld(__amdgpu_buffer_rsrc_t rs, uint32_t xb, uint32_t soff) {
     Row<CW> r;
     if constexpr (CW == 4) {
-        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, xb, soff, kRowCachePolicy);
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, xb, soff, POLICY);
         r.v[0] = v.x; r.v[1] = v.y; r.v[2] = v.z; r.v[3] = v.w;
     } else if constexpr (CW == 2) {
-        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rs, xb, soff, kRowCachePolicy);
+        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rs, xb, soff, POLICY);
         r.v[0] = v.x; r.v[1] = v.y;
     } else {
-        r.v[0] = __builtin_amdgcn_raw_buffer_load_b32(rs, xb, soff, kRowCachePolicy);
+        r.v[0] = __builtin_amdgcn_raw_buffer_load_b32(rs, xb, soff, POLICY);
     }
     return r;
 }
@@ -75,16 +79,16 @@ __device__ __forceinline__ Row<CW> ld(__amdgpu_buffer_rsrc_t rs, uint32_t xb, ui
 // the scalar offset field the compiler does not keep the next instructions
 // from overwriting them (seen on gfx950 as wrong words in the last lanes of
 // each group of 16); with a constant there it does.
-template <int CW>
+template <int CW, int POLICY = kRowCachePolicy>
 __device__ __forceinline__ void st(__amdgpu_buffer_rsrc_t rs, uint32_t off, const Row<CW>& r) {
     if constexpr (CW == 4) {
         const u32x4 v = {r.v[0], r.v[1], r.v[2], r.v[3]};
-        __builtin_amdgcn_raw_buffer_store_b128(v, rs, off, 0, kRowCachePolicy);
+        __builtin_amdgcn_raw_buffer_store_b128(v, rs, off, 0, POLICY);
     } else if constexpr (CW == 2) {
         const u32x2 v = {r.v[0], r.v[1]};
-        __builtin_amdgcn_raw_buffer_store_b64(v, rs, off, 0, kRowCachePolicy);
+        __builtin_amdgcn_raw_buffer_store_b64(v, rs, off, 0, POLICY);
     } else {
-        __builtin_amdgcn_raw_buffer_store_b32(r.v[0], rs, off, 0, kRowCachePolicy);
+        __builtin_amdgcn_raw_buffer_store_b32(r.v[0], rs, off, 0, POLICY);
     }
 }
 

@@ -17,6 +17,14 @@ struct Planes {
     uint32_t Hw;    // H / 4 (meaningful when L % 8 == 0)
 };
 
+// Whether sweeps that ping-pong `sites` sites in all find their rows in the
+// 256 MB cache (two bytes a site), so that rows are loaded and stored without
+// the nontemporal hint. Us a sweep with the hint and without, by MB of both
+// buffers: a stepped batch 168 MB 66.1 and 61.2, 203 78.9 and 74.8, 240 88.7
+// and 85.6, 315 108.2 and 109.2; tiles of one lattice 128 MB (8192^2) 42.7 and
+// 37.8, 191 63.9 and 58.2, 256 80.7 and 73.8; 32768^2 (2 GB) 450 and 487.
+inline bool rows_stay_cached(uint64_t sites) { return 2u * sites <= ((uint64_t)256 << 20); }
+
 // Arguments of the fused one-pass sweep (ising_fused.hip).
 struct FusedArgs {
     const uint32_t* src0;  // lattice of sweep t-1, colour planes 0 and 1
@@ -225,7 +233,7 @@ uint32_t multi_fused_tiles(uint32_t L, uint32_t rows);
 // Waves of the fused walk resident at once on a GPU with `cus` compute units.
 uint32_t multi_fused_wave_slots(uint32_t cus);
 hipError_t launch_multi_fused_graph_body(const BatchItem* items, const uint32_t* tile_start, MultiHeader* hdr,
-                                         uint32_t sweeps_per_replay, uint32_t grid, hipStream_t s);
+                                         uint32_t sweeps_per_replay, uint32_t grid, bool cached, hipStream_t s);
 
 // Creutz demon dynamics (ising_creutz.hip): dm holds the demon planes, in
 // the spin planes' layout. A sweep is two in-place passes; the word path

@@ -40,6 +40,7 @@ __device__ __forceinline__ uint32_t wrap_row_m(int i, uint32_t L) {
 }
 
 // Partial (B, M) of one tile of item `it` for its sweep `s` of this call.
+template <int POLICY>
 __device__ __forceinline__ void mf_tile(const LdsTable& lt, const BatchItem& it, uint32_t tx, uint32_t ty,
                                         uint32_t rows, uint32_t s, int64_t& b_out, int64_t& m_out) {
     constexpr int CW = kMfCW;
@@ -101,29 +102,29 @@ __device__ __forceinline__ void mf_tile(const LdsTable& lt, const BatchItem& it,
     auto rword = [&](int i) { return wrap_row_m(i, L) * Hw; };
     auto rbyte = [&](int i) { return rword(i) * 4u; };
     Row<CW> c1[4], c0o[2], c0n[4];
-    const Row<CW> c1m2 = ld<CW>(rs1, xb, rbyte(r0 - 2));
-    const Row<CW> c1m1 = ld<CW>(rs1, xb, rbyte(r0 - 1));
-    c1[0] = ld<CW>(rs1, xb, rbyte(r0));
-    c1[1] = ld<CW>(rs1, xb, rbyte(r0 + 1));
-    c1[2] = ld<CW>(rs1, xb, rbyte(r0 + 2));
-    const Row<CW> c0om1 = ld<CW>(rs0, xb, rbyte(r0 - 1));
-    c0o[0] = ld<CW>(rs0, xb, rbyte(r0));
-    c0o[1] = ld<CW>(rs0, xb, rbyte(r0 + 1));
+    const Row<CW> c1m2 = ld<CW, POLICY>(rs1, xb, rbyte(r0 - 2));
+    const Row<CW> c1m1 = ld<CW, POLICY>(rs1, xb, rbyte(r0 - 1));
+    c1[0] = ld<CW, POLICY>(rs1, xb, rbyte(r0));
+    c1[1] = ld<CW, POLICY>(rs1, xb, rbyte(r0 + 1));
+    c1[2] = ld<CW, POLICY>(rs1, xb, rbyte(r0 + 2));
+    const Row<CW> c0om1 = ld<CW, POLICY>(rs0, xb, rbyte(r0 - 1));
+    c0o[0] = ld<CW, POLICY>(rs0, xb, rbyte(r0));
+    c0o[1] = ld<CW, POLICY>(rs0, xb, rbyte(r0 + 1));
     const uint32_t eR = row_ptr(s1, r0 - 1)[xr];
     const uint32_t eL = row_ptr(s1, r0)[xl];
     c0n[0] = update_row<CW, 1, false, true>(lt, c0om1, c1m2, c1[0], c1m1, eR, xw, rword(r0 - 1), t, 0u, k0,
                                                    k1, dummy, is_last);
     c0n[1] = update_row<CW, 0, false, true>(lt, c0o[0], c1m1, c1[1], c1[0], eL, xw, rword(r0), t, 0u, k0,
                                                    k1, dummy, is_last);
-    if (active) st<CW>(rd0, xb + rbyte(r0), c0n[1]);
+    if (active) st<CW, POLICY>(rd0, xb + rbyte(r0), c0n[1]);
 
 #pragma unroll 1
     for (int k = 0; k < R; k += 4) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int i = r0 + k + u;
-            c1[(u + 3) & 3] = ld<CW>(rs1, xb, rbyte(i + 3));
-            c0o[u & 1] = ld<CW>(rs0, xb, rbyte(i + 2));
+            c1[(u + 3) & 3] = ld<CW, POLICY>(rs1, xb, rbyte(i + 3));
+            c0o[u & 1] = ld<CW, POLICY>(rs0, xb, rbyte(i + 2));
             const uint32_t e1 = (uint32_t)__builtin_amdgcn_readlane((int)edge_c1, k + u);
             const uint32_t e0 = (uint32_t)__builtin_amdgcn_readlane((int)edge_c0, k + u);
             const uint32_t m1 = rword(i + 1);
@@ -143,8 +144,8 @@ __device__ __forceinline__ void mf_tile(const LdsTable& lt, const BatchItem& it,
                                                            c0n[(u + 1) & 3], e0, xw, m0, t, 1u, k0, k1, sad, is_last);
             }
             if (active) {
-                if (k + u + 1 < R) st<CW>(rd0, xb + rbyte(i + 1), c0n[(u + 2) & 3]);
-                st<CW>(rd1, xb + rbyte(i), c1n);
+                if (k + u + 1 < R) st<CW, POLICY>(rd0, xb + rbyte(i + 1), c0n[(u + 2) & 3]);
+                st<CW, POLICY>(rd1, xb + rbyte(i), c1n);
             }
 #pragma unroll
             for (int w = 0; w < CW; ++w) ups8 += c1n.v[w] + c0n[(u + 1) & 3].v[w];
@@ -177,6 +178,7 @@ __device__ __forceinline__ void mf_tile(const LdsTable& lt, const BatchItem& it,
 // in step; each lane addresses its band's rows through its own offsets. The
 // edge words of band b's rows are computed by lanes b rows .. b rows +
 // rows - 1 and fetched with a lane permute.
+template <int POLICY>
 __device__ __forceinline__ void mf_tile_packed(const LdsTable& lt, const BatchItem& it, uint32_t tx, uint32_t ty0,
                                                uint32_t bands, uint32_t rows, uint32_t s, int64_t& b_out,
                                                int64_t& m_out) {
@@ -248,21 +250,21 @@ __device__ __forceinline__ void mf_tile_packed(const LdsTable& lt, const BatchIt
     vo[0] = vrow(0);
     vo[1] = vrow(1);
     vo[2] = vrow(2);
-    const Row<CW> c1m2 = ld<CW>(rs1, vm2, 0u);
-    const Row<CW> c1m1 = ld<CW>(rs1, vm1, 0u);
-    c1[0] = ld<CW>(rs1, vo[0], 0u);
-    c1[1] = ld<CW>(rs1, vo[1], 0u);
-    c1[2] = ld<CW>(rs1, vo[2], 0u);
-    const Row<CW> c0om1 = ld<CW>(rs0, vm1, 0u);
-    c0o[0] = ld<CW>(rs0, vo[0], 0u);
-    c0o[1] = ld<CW>(rs0, vo[1], 0u);
+    const Row<CW> c1m2 = ld<CW, POLICY>(rs1, vm2, 0u);
+    const Row<CW> c1m1 = ld<CW, POLICY>(rs1, vm1, 0u);
+    c1[0] = ld<CW, POLICY>(rs1, vo[0], 0u);
+    c1[1] = ld<CW, POLICY>(rs1, vo[1], 0u);
+    c1[2] = ld<CW, POLICY>(rs1, vo[2], 0u);
+    const Row<CW> c0om1 = ld<CW, POLICY>(rs0, vm1, 0u);
+    c0o[0] = ld<CW, POLICY>(rs0, vo[0], 0u);
+    c0o[1] = ld<CW, POLICY>(rs0, vo[1], 0u);
     const uint32_t eR = row_ptr(s1, rb - 1)[xr];
     const uint32_t eL = row_ptr(s1, rb)[xl];
     c0n[0] = update_row<CW, 1, false, true, true>(lt, c0om1, c1m2, c1[0], c1m1, eR, xw, m0of(vm1), t, 0u, k0,
                                                          k1, dummy, is_last, is_first);
     c0n[1] = update_row<CW, 0, false, true, true>(lt, c0o[0], c1m1, c1[1], c1[0], eL, xw, m0of(vo[0]), t, 0u,
                                                          k0, k1, dummy, is_last, is_first);
-    if (active) st<CW>(rd0, vo[0], c0n[1]);
+    if (active) st<CW, POLICY>(rd0, vo[0], c0n[1]);
 
     const int eb0 = (int)(bl * rows) * 4;  // byte index of this band's first edge lane
 #pragma unroll 1
@@ -271,8 +273,8 @@ __device__ __forceinline__ void mf_tile_packed(const LdsTable& lt, const BatchIt
         for (int u = 0; u < 4; ++u) {
             const int i = k + u;  // row rb + i
             vo[(u + 3) & 3] = vrow(i + 3);
-            c1[(u + 3) & 3] = ld<CW>(rs1, vo[(u + 3) & 3], 0u);
-            c0o[u & 1] = ld<CW>(rs0, vo[(u + 2) & 3], 0u);
+            c1[(u + 3) & 3] = ld<CW, POLICY>(rs1, vo[(u + 3) & 3], 0u);
+            c0o[u & 1] = ld<CW, POLICY>(rs0, vo[(u + 2) & 3], 0u);
             const uint32_t e1 = (uint32_t)__builtin_amdgcn_ds_bpermute(eb0 + 4 * i, (int)edge_c1);
             const uint32_t e0 = (uint32_t)__builtin_amdgcn_ds_bpermute(eb0 + 4 * i, (int)edge_c0);
             const uint32_t m1 = m0of(vo[(u + 1) & 3]);
@@ -294,8 +296,8 @@ __device__ __forceinline__ void mf_tile_packed(const LdsTable& lt, const BatchIt
                                                                  is_last, is_first);
             }
             if (active) {
-                if (i + 1 < R) st<CW>(rd0, vo[(u + 1) & 3], c0n[(u + 2) & 3]);
-                st<CW>(rd1, vo[u & 3], c1n);
+                if (i + 1 < R) st<CW, POLICY>(rd0, vo[(u + 1) & 3], c0n[(u + 2) & 3]);
+                st<CW, POLICY>(rd1, vo[u & 3], c1n);
             }
 #pragma unroll
             for (int w = 0; w < CW; ++w) ups8 += c1n.v[w] + c0n[(u + 1) & 3].v[w];
@@ -321,6 +323,7 @@ __device__ __forceinline__ void mf_tile_packed(const LdsTable& lt, const BatchIt
 
 // Sweep hdr->s_base + s of every item with that sweep pending. Waves take
 // virtual tiles (tile_start[k] = item k's first) in a grid-stride loop.
+template <int POLICY>
 __global__ void __launch_bounds__(kMfThreads) k_multi_fused(const BatchItem* __restrict__ items,
                                                             const uint32_t* __restrict__ tile_start,
                                                             const MultiHeader* __restrict__ hdr, uint32_t s) {
@@ -351,11 +354,11 @@ __global__ void __launch_bounds__(kMfThreads) k_multi_fused(const BatchItem* __r
         if (lay.pack > 1u && tile >= full) {
             const uint32_t ty0 = (tile - full) * lay.pack;
             const uint32_t bands = min(lay.pack, lay.n_typ - ty0);
-            mf_tile_packed(lt[wv], it, lay.n_tx - 1u, ty0, bands, lay.prow, sweep, b, m);
+            mf_tile_packed<POLICY>(lt[wv], it, lay.n_tx - 1u, ty0, bands, lay.prow, sweep, b, m);
         } else {
             const uint32_t cols = lay.pack > 1u ? lay.n_tx - 1u : lay.n_tx;
             const uint32_t tx = tile % cols, ty = tile / cols;
-            mf_tile(lt[wv], it, tx, ty, rows, sweep, b, m);
+            mf_tile<POLICY>(lt[wv], it, tx, ty, rows, sweep, b, m);
         }
         if (lane == 0) {
             part[2ull * g] = b;
@@ -406,7 +409,7 @@ uint32_t multi_fused_tiles(uint32_t L, uint32_t rows) { return mf_layout(L, rows
 
 uint32_t multi_fused_wave_slots(uint32_t cus) {
     int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_multi_fused, (int)kMfThreads, 0) != hipSuccess ||
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_multi_fused<kRowCachePolicy>, (int)kMfThreads, 0) != hipSuccess ||
         per_cu < 1) {
         (void)hipGetLastError();
         per_cu = 1;
@@ -425,10 +428,10 @@ __global__ void __launch_bounds__(64) k_multi_fused_advance(MultiHeader* hdr, ui
 }
 
 hipError_t launch_multi_fused_graph_body(const BatchItem* items, const uint32_t* tile_start, MultiHeader* hdr,
-                                         uint32_t sweeps_per_replay, uint32_t grid, hipStream_t s) {
+                                         uint32_t sweeps_per_replay, uint32_t grid, bool cached, hipStream_t s) {
     k_multi_fused_advance<<<1, 64, 0, s>>>(hdr, sweeps_per_replay);
-    for (uint32_t k = 0; k < sweeps_per_replay; ++k)
-        k_multi_fused<<<grid, kMfThreads, 0, s>>>(items, tile_start, hdr, k);
+    const auto kernel = cached ? k_multi_fused<kRowCachePlain> : k_multi_fused<kRowCachePolicy>;
+    for (uint32_t k = 0; k < sweeps_per_replay; ++k) kernel<<<grid, kMfThreads, 0, s>>>(items, tile_start, hdr, k);
     hipError_t r = hipGetLastError();
     if (r != hipSuccess) return r;
     return launch_multi_reduce(items, tile_start, hdr, sweeps_per_replay, grid, s);

@@ -15,7 +15,8 @@
 // 32760^2 514 and 525). Us a sweep on one MI355X,
 // before and now: lattices in a field, whose band update by bits costs half as
 // much again as without, 4104^2 27.2 and 19.5, 8192^2 51.0 and 46.2, 10000^2
-// 88.2 and 70.8, 12296^2 145 and 99, 16384^2 182 and 156; sides beyond the
+// 88.2 and 70.8 (and, without the nontemporal hint where the buffers stay in
+// cache, 18.1, 37.8 and 58.2), 12296^2 145 and 99, 16384^2 182 and 156; sides beyond the
 // bands, by two passes, 16392^2 216 and 177, 18000^2 239 and 190, 20000^2 264
 // and 225, 26008^2 545 and 350, 32760^2 856 and 525 (2042 site updates/ns, 4.1
 // TB/s). Whole columns only (sides of 512) stay with k_fused, 5% faster for
@@ -78,7 +79,7 @@ __device__ __forceinline__ Row<CW> update_part(const LdsTable& lt, const Part<CW
 
 // One tile: R rows from r0, the columns from word X0 (PART: `wds` words of
 // them, fewer than 64 CW). The rows are those of k_fused (ising_fused.hip).
-template <int CW, bool PART>
+template <int CW, bool PART, int POLICY>
 __device__ __forceinline__ void walk(const LdsTable& lt, const FusedArgs& a, uint32_t X0, uint32_t wds, int r0, int R,
                                      int64_t* out) {
     const uint32_t lane = threadIdx.x & 63u;
@@ -139,11 +140,11 @@ __device__ __forceinline__ void walk(const LdsTable& lt, const FusedArgs& a, uin
     auto rbyte = [&](int i) { return rword(i) * 4u; };
     auto store = [&](__amdgpu_buffer_rsrc_t rs, uint32_t off, const Row<CW>& r) {
         if (!PART || pt.words == CW) {
-            st<CW>(rs, off, r);
+            st<CW, POLICY>(rs, off, r);
         } else {
 #pragma unroll
             for (int v = 0; v < CW; ++v)
-                if (pt.keep[v]) __builtin_amdgcn_raw_buffer_store_b32(r.v[v], rs, off + 4u * (uint32_t)v, 0, kRowCachePolicy);
+                if (pt.keep[v]) __builtin_amdgcn_raw_buffer_store_b32(r.v[v], rs, off + 4u * (uint32_t)v, 0, POLICY);
         }
     };
     // colour 0 of a row (not counted) and colour 1 (counted)
@@ -167,14 +168,14 @@ __device__ __forceinline__ void walk(const LdsTable& lt, const FusedArgs& a, uin
     // rings: c1[(row - r0) & 3] old colour-1 rows, c0o[(row - r0) & 1] old
     // colour-0 rows, c0n[(row - r0 + 1) & 3] new colour-0 rows
     Row<CW> c1[4], c0o[2], c0n[4];
-    const Row<CW> c1m2 = ld<CW>(rs1, xb, rbyte(r0 - 2));
-    const Row<CW> c1m1 = ld<CW>(rs1, xb, rbyte(r0 - 1));
-    c1[0] = ld<CW>(rs1, xb, rbyte(r0));
-    c1[1] = ld<CW>(rs1, xb, rbyte(r0 + 1));
-    c1[2] = ld<CW>(rs1, xb, rbyte(r0 + 2));
-    const Row<CW> c0om1 = ld<CW>(rs0, xb, rbyte(r0 - 1));
-    c0o[0] = ld<CW>(rs0, xb, rbyte(r0));
-    c0o[1] = ld<CW>(rs0, xb, rbyte(r0 + 1));
+    const Row<CW> c1m2 = ld<CW, POLICY>(rs1, xb, rbyte(r0 - 2));
+    const Row<CW> c1m1 = ld<CW, POLICY>(rs1, xb, rbyte(r0 - 1));
+    c1[0] = ld<CW, POLICY>(rs1, xb, rbyte(r0));
+    c1[1] = ld<CW, POLICY>(rs1, xb, rbyte(r0 + 1));
+    c1[2] = ld<CW, POLICY>(rs1, xb, rbyte(r0 + 2));
+    const Row<CW> c0om1 = ld<CW, POLICY>(rs0, xb, rbyte(r0 - 1));
+    c0o[0] = ld<CW, POLICY>(rs0, xb, rbyte(r0));
+    c0o[1] = ld<CW, POLICY>(rs0, xb, rbyte(r0 + 1));
     const uint32_t eR = row_ptr(s1, r0 - 1)[xr];
     const uint32_t eL = row_ptr(s1, r0)[xl];
     c0n[0] = first(Step<1>{}, c0om1, c1m2, c1[0], c1m1, eR, rword(r0 - 1));
@@ -186,8 +187,8 @@ __device__ __forceinline__ void walk(const LdsTable& lt, const FusedArgs& a, uin
         auto step = [&](auto uc) {
             constexpr int u = decltype(uc)::value;
             const int i = r0 + k + u;
-            c1[(u + 3) & 3] = ld<CW>(rs1, xb, rbyte(i + 3));
-            c0o[u & 1] = ld<CW>(rs0, xb, rbyte(i + 2));
+            c1[(u + 3) & 3] = ld<CW, POLICY>(rs1, xb, rbyte(i + 3));
+            c0o[u & 1] = ld<CW, POLICY>(rs0, xb, rbyte(i + 2));
             const uint32_t e1 = (uint32_t)__builtin_amdgcn_readlane((int)edge_c1, k + u);
             const uint32_t e0 = (uint32_t)__builtin_amdgcn_readlane((int)edge_c0, k + u);
             using P = Step<(u & 1) == 0 ? 1 : 0>;
@@ -227,7 +228,7 @@ __device__ __forceinline__ void walk(const LdsTable& lt, const FusedArgs& a, uin
 }
 
 // At least four waves per SIMD (at most 128 registers).
-template <int CW>
+template <int CW, int POLICY>
 __global__ void __launch_bounds__(kThreads, 4) k_tiles(FusedArgs a, AcceptTable at, PartialReduce red, uint32_t rows) {
     __shared__ LdsTable lt;
     load_table(lt, at);
@@ -240,8 +241,8 @@ __global__ void __launch_bounds__(kThreads, 4) k_tiles(FusedArgs a, AcceptTable 
     const uint32_t X0 = tx * 64u * CW, wds = min(64u * CW, a.Hw - X0);
     const int r0 = (int)(ty * rows), R = (int)min(rows, a.L - ty * rows);  // a multiple of 4: L % 8 == 0
     int64_t* const out = a.part + 2ull * tile;
-    if (wds == 64u * CW) walk<CW, false>(lt, a, X0, wds, r0, R, out);
-    else walk<CW, true>(lt, a, X0, wds, r0, R, out);
+    if (wds == 64u * CW) walk<CW, false, POLICY>(lt, a, X0, wds, r0, R, out);
+    else walk<CW, true, POLICY>(lt, a, X0, wds, r0, R, out);
 }
 
 }  // namespace
@@ -264,8 +265,10 @@ hipError_t launch_tiles(const FusedArgs& a, const AcceptTable& at, const TileSha
                         hipStream_t s) {
     // whole groups of eight blocks, one for each chiplet (xcd_block)
     const uint32_t blocks = (shape.tiles + 8u * (kThreads / 64u) - 1u) / (8u * (kThreads / 64u)) * 8u;
-    if (shape.cw == 2u) k_tiles<2><<<blocks, kThreads, 0, s>>>(a, at, red, shape.rows);
-    else k_tiles<4><<<blocks, kThreads, 0, s>>>(a, at, red, shape.rows);
+    const auto kernel = shape.cw != 2u                          ? k_tiles<4, kRowCachePolicy>
+                        : rows_stay_cached((uint64_t)a.L * a.L) ? k_tiles<2, kRowCachePlain>
+                                                                : k_tiles<2, kRowCachePolicy>;
+    kernel<<<blocks, kThreads, 0, s>>>(a, at, red, shape.rows);
     return hipGetLastError();
 }
 

@@ -36,6 +36,7 @@ def _run(b, L, calls, **p):
     (6136, 1.0, -0.3, 1.0, (4,)),     # a last lane of one word, 63 lanes whole
     (8192, 1.0, 0.1, 0.05, (2,)),     # whole columns, 16-row tiles; zero and certain thresholds
     (8200, 1.0, 0.1, 2.3, (3, 2)),    # a last band of 8 rows
+    (12296, 1.0, 0.1, 2.3, (2,)),     # buffers beyond the cache
     (16392, 1.0, 0.0, 2.3, (3,)),     # four words a lane, the last column one word
     (18432, 1.0, 0.0, 2.3, (2,)),     # whole columns: the fused tiles, in place of full rows
     (20024, 1.0, 0.0, 0.05, (2,)),    # three words of the last lane
@@ -55,6 +56,32 @@ def test_tiles_match_the_per_site_plan_and_the_oracle(b, L, J, h, T, calls):
         win, valid = o.window_run(L, J, h, T, p["seed"], 0, n, i0, j0, win)
         got = s[np.ix_((np.arange(wide) + i0) % L, (np.arange(wide) + j0) % L)]
         assert valid.any() and np.array_equal(got[valid], win[valid])
+
+
+def test_stepped_batches_beyond_and_within_the_cache(b):
+    """The same lattices stepped in one batch of 302 MB (both buffers) and in
+    two of 67 and 235 MB."""
+    sides = [4096] * 2 + [4096, 4080, 4064, 4096, 4048, 4096, 4032]
+    G.log("stepped batches around the cache's size")
+    one = [b.ising_create(L, h=0.02, T=2.3, seed=L + k) for k, L in enumerate(sides)]
+    two = [b.ising_create(L, h=0.02, T=2.3, seed=L + k) for k, L in enumerate(sides)]
+    try:
+        b.ising_sweep_batch_plan(one, [3] * 9, b.ISING_BATCH_STEPPED)
+        for part in (two[:2], two[2:]):
+            b.ising_sweep_batch_plan(part, [3] * len(part), b.ISING_BATCH_STEPPED)
+        for k, L in enumerate(sides):
+            (_, B, M), (_, B2, M2) = (b.ising_observables(c[k], b.ISING_OBS_SERIES) for c in (one, two))
+            assert np.array_equal(B, B2) and np.array_equal(M, M2)
+            assert np.array_equal(b.ising_copy_spins(one[k], L), b.ising_copy_spins(two[k], L))
+        r = b.ising_create(sides[3], h=0.02, T=2.3, seed=sides[3] + 3)
+        try:
+            b.ising_sweep(r, 3)
+            assert np.array_equal(b.ising_copy_spins(r, sides[3]), b.ising_copy_spins(one[3], sides[3]))
+        finally:
+            b.ising_destroy(r)
+    finally:
+        for c in one + two:
+            b.ising_destroy(c)
 
 
 @pytest.mark.parametrize("L,h,creutz", [(4104, 0.1, False), (4104, 0.0, True)])
