@@ -420,8 +420,8 @@ static uint32_t generic_bands(const ising_ctx* ctx) {
 
 // Partial sums of a sweep's tiles, bands or blocks: two buffers of at least
 // `need` pairs. On failure those there were stay.
-static int ctx_parts(ising_ctx* ctx, uint32_t need) {
-    if (need <= ctx->part_cap) return ISING_OK;
+static int grow_parts(int64_t* (&part)[2], uint32_t* cap, uint32_t need) {
+    if (need <= *cap) return ISING_OK;
     int64_t* fresh[2] = {nullptr, nullptr};
     for (int k = 0; k < 2; ++k) {
         if (hipMalloc(&fresh[k], (size_t)need * 2 * sizeof(int64_t)) != hipSuccess) {
@@ -431,10 +431,10 @@ static int ctx_parts(ising_ctx* ctx, uint32_t need) {
         }
     }
     for (int k = 0; k < 2; ++k) {
-        if (ctx->part[k]) (void)hipFree(ctx->part[k]);  // waits for the device
-        ctx->part[k] = fresh[k];
+        if (part[k]) (void)hipFree(part[k]);  // waits for the device
+        part[k] = fresh[k];
     }
-    ctx->part_cap = need;
+    *cap = need;
     return ISING_OK;
 }
 
@@ -476,7 +476,7 @@ int ctx_prepare_plan(ising_ctx* ctx) {
     if (ctx->plan.kind == ISING_PLAN_FUSED) need = fused_tiles(ctx->L, ctx->plan.cw, ctx->plan.rows);
     if (ctx->plan.kind == ISING_PLAN_FUSED_ROWS) need = fused_rows_bands(ctx->L, ctx->plan.rows);
     if (ctx->plan.kind == ISING_PLAN_TWO_PASS) need = two_pass_blocks(pl, ctx->plan.cw);
-    return ctx_parts(ctx, need);
+    return grow_parts(ctx->part, &ctx->part_cap, need);
 }
 
 static size_t state_bytes_for(uint32_t L, const Plan& pl) {
@@ -863,7 +863,7 @@ static int sweep_tiles(ising_ctx* ctx, uint64_t n, int64_t* ser, bool* served) {
     TileShape shape;
     if (n < 2 || !tiles_serve(ctx) || stream_capturing(ctx->stream) || !tiles_shape(ctx->L, &shape)) return ISING_OK;
     int rc = ctx_second_buffer(ctx);
-    if (rc == ISING_OK) rc = ctx_parts(ctx, shape.tiles);
+    if (rc == ISING_OK) rc = grow_parts(ctx->tile_part, &ctx->tile_part_cap, shape.tiles);
     if (rc != ISING_OK) return rc == ISING_ENOMEM ? ISING_OK : rc;
     const int home = ctx->cur;
     for (uint64_t k = 0; k < n; ++k) {
@@ -871,13 +871,13 @@ static int sweep_tiles(ising_ctx* ctx, uint64_t n, int64_t* ser, bool* served) {
         const FusedArgs a{reinterpret_cast<const uint32_t*>(src.p[0]), reinterpret_cast<const uint32_t*>(src.p[1]),
                           reinterpret_cast<uint32_t*>(dst.p[0]), reinterpret_cast<uint32_t*>(dst.p[1]),
                           ctx->L, ctx->L / 8u, (uint32_t)(ctx->t + k), (uint32_t)ctx->p.seed,
-                          (uint32_t)(ctx->p.seed >> 32), shape.n_tx, shape.tiles, ctx->part[k & 1]};
+                          (uint32_t)(ctx->p.seed >> 32), shape.n_tx, shape.tiles, ctx->tile_part[k & 1]};
         PartialReduce red{nullptr, 0, nullptr};
-        if (k > 0) red = PartialReduce{ctx->part[(k - 1) & 1], shape.tiles, ser + 2 * (k - 1)};
+        if (k > 0) red = PartialReduce{ctx->tile_part[(k - 1) & 1], shape.tiles, ser + 2 * (k - 1)};
         HIP_TRY(ctx, launch_tiles(a, ctx->table, shape, red, ctx->stream));
         ctx->cur ^= 1;
     }
-    HIP_TRY(ctx, launch_reduce_partials(PartialReduce{ctx->part[(n - 1) & 1], shape.tiles, ser + 2 * (n - 1)},
+    HIP_TRY(ctx, launch_reduce_partials(PartialReduce{ctx->tile_part[(n - 1) & 1], shape.tiles, ser + 2 * (n - 1)},
                                         ctx->stream));
     *served = true;
     return ctx_to_buffer(ctx, home);
@@ -1562,21 +1562,7 @@ static int creutz_fused_prepare(ising_ctx* ctx, uint32_t cw, uint32_t rows) {
     const int rc = creutz_second_buffers(ctx);
     if (rc != ISING_OK) return rc;
     const uint32_t need = fused_tiles(ctx->L, cw, rows);
-    if (need > ctx->cfpart_cap) {
-        for (int k = 0; k < 2; ++k) {
-            if (ctx->cfpart[k]) (void)hipFree(ctx->cfpart[k]);
-            ctx->cfpart[k] = nullptr;
-        }
-        ctx->cfpart_cap = 0;
-        for (int k = 0; k < 2; ++k) {
-            if (hipMalloc(&ctx->cfpart[k], (size_t)need * 2 * sizeof(int64_t)) != hipSuccess) {
-                (void)hipGetLastError();
-                return ISING_ENOMEM;
-            }
-        }
-        ctx->cfpart_cap = need;
-    }
-    return ISING_OK;
+    return grow_parts(ctx->cfpart, &ctx->cfpart_cap, need);
 }
 
 // n fused Creutz sweeps; series slots ser[0 .. 2n).
@@ -1780,8 +1766,10 @@ int ising_destroy(ising_ctx* ctx) {
     if (ctx->band_pub) (void)hipFree(ctx->band_pub);
     if (ctx->band_part) (void)hipFree(ctx->band_part);
     if (ctx->band_err_host) (void)hipHostFree(ctx->band_err_host);
-    for (int k = 0; k < 2; ++k)
+    for (int k = 0; k < 2; ++k) {
         if (ctx->cfpart[k]) (void)hipFree(ctx->cfpart[k]);
+        if (ctx->tile_part[k]) (void)hipFree(ctx->tile_part[k]);
+    }
     if (ctx->scratch) (void)hipFree(ctx->scratch);
     if (ctx->canon) (void)hipFree(ctx->canon);
     if (ctx->host_stage) (void)hipHostFree(ctx->host_stage);

@@ -45,6 +45,8 @@ struct ising_ctx {
     uint64_t series_len = 0;
     int64_t* part[2] = {nullptr, nullptr};  // per-tile / per-block partials
     uint32_t part_cap = 0;       // pairs per partial buffer
+    int64_t* tile_part[2] = {nullptr, nullptr};  // the same for sweeps over wave tiles of any row length
+    uint32_t tile_part_cap = 0;
     int64_t* scratch = nullptr;  // 4 int64 for observables
     int8_t* canon = nullptr;     // N bytes, canonical layout staging
     void* host_stage = nullptr;  // pinned host memory the observables are read back into
