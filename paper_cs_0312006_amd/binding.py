@@ -7,6 +7,7 @@ streams may come from PyTorch: pass ``tensor.data_ptr()`` and
 """
 import ctypes as C
 import os
+import threading
 
 import numpy as np
 
@@ -224,6 +225,19 @@ def ising_sweep_static(ctx, n, series_dev):
     _check(lib().ising_sweep_static(ctx, int(n), C.c_void_p(int(series_dev))), "ising_sweep_static", ctx)
 
 
+_thread = threading.local()
+
+
+def _series_room():
+    """This thread's room for a short series (bond and magnetisation sums):
+    kept, so that a caller's arrays are the only ones a call allocates."""
+    try:
+        return _thread.series_room
+    except AttributeError:
+        _thread.series_room = np.empty((2, 4096), dtype=np.int64)
+        return _thread.series_room
+
+
 def ising_observables(ctx, want=0, capacity=None):
     """Returns (ising_obs, bond_series or None, mag_series or None)."""
     obs = ising_obs()
@@ -234,12 +248,12 @@ def ising_observables(ctx, want=0, capacity=None):
         if capacity is None:
             # a series of up to 4096 sweeps comes in one read-back; a longer
             # one is refused before any device work, and its length asked for
-            bs = np.empty(4096, dtype=np.int64)
-            ms = np.empty(4096, dtype=np.int64)
-            rc = lib().ising_observables(ctx, C.byref(obs), bs.ctypes.data, ms.ctypes.data, 4096, int(want))
+            room = _series_room()
+            rc = lib().ising_observables(ctx, C.byref(obs), room.ctypes.data, room[1].ctypes.data, room.shape[1],
+                                         int(want))
             if rc != ISING_ERANGE:
                 _check(rc, "ising_observables", ctx)
-                return obs, bs[:obs.series_len].copy(), ms[:obs.series_len].copy()
+                return obs, room[0, :obs.series_len].copy(), room[1, :obs.series_len].copy()
             rc = lib().ising_observables(ctx, C.byref(obs), None, None, 0, 0)
             _check(rc, "ising_observables")
             capacity = obs.series_len
