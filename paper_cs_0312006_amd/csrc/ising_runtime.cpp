@@ -1628,13 +1628,22 @@ static int creutz_sweep_bands(ising_ctx* ctx, uint64_t n, bool reverse, int64_t*
     return ISING_OK;
 }
 
-// The even part of n Creutz sweeps two a launch, for sides beyond the bands;
-// returns the sweeps left (all of them where this is not served: captured
-// streams, sides of partial words or beyond 32768, no room for the buffers).
+// Creutz sweeps two a launch, for sides beyond the bands; returns the sweeps
+// left (all of them where this is not served: captured streams, sides of
+// partial words or beyond 32768, no room for the buffers).
+//
+// Each launch moves spins and demons to their other buffers. A call ends in the
+// buffers where n single sweeps end, whose addresses graphs that a caller
+// captured hold: launches are run by twos, and after an odd one both are copied
+// back or, up to 6144, its two sweeps left to the single-sweep kernels. Us for
+// a call of two sweeps, two single ones against a launch and the copies: 4104^2
+// 55 and 63, 5000^2 65 and 72, 6136^2 86 and 91, 7168^2 110 and 100, 8192^2 146
+// and 117, 10000^2 178 and 184, 12296^2 344 and 278, 16384^2 518 and 419.
 static int creutz_sweep_pairs(ising_ctx* ctx, uint64_t n, bool reverse, int64_t* ser, uint64_t* left) {
     *left = n;
     const uint32_t L = ctx->L;
-    if (n < 2 || row_bands_serve(L, band_count(L, band_default_rows(L)), true) || stream_capturing(ctx->stream))
+    const uint64_t pairs = L > 6144u ? n / 2 : n / 4 * 2;
+    if (pairs == 0 || row_bands_serve(L, band_count(L, band_default_rows(L)), true) || stream_capturing(ctx->stream))
         return ISING_OK;
     int cus = 0;
     HIP_TRY(ctx, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device));
@@ -1645,7 +1654,6 @@ static int creutz_sweep_pairs(ising_ctx* ctx, uint64_t n, bool reverse, int64_t*
     if (rc == ISING_ENOMEM) return ISING_OK;
     if (rc != ISING_OK) return rc;
     const uint32_t f = reverse ? 1u : 0u;  // the colour of a sweep's first half
-    const uint64_t pairs = n / 2;
     const int home = ctx->cur;
     for (uint64_t done = 0; done < pairs;) {
         const uint32_t m = (uint32_t)std::min<uint64_t>(pairs - done, kBandChunk / 2);
@@ -1665,9 +1673,10 @@ static int creutz_sweep_pairs(ising_ctx* ctx, uint64_t n, bool reverse, int64_t*
         done += m;
     }
     *left = n - 2 * pairs;
-    // as in place, where single sweeps are
-    uint32_t cw = 0, rows = 0;
-    return reverse || !default_fused(L, &cw, &rows) ? ctx_to_buffer(ctx, home) : ISING_OK;
+    if (pairs % 2 == 0) return ISING_OK;
+    HIP_TRY(ctx, hipMemcpyAsync(ctx->demon_alt, ctx->demon, (size_t)L * L, hipMemcpyDeviceToDevice, ctx->stream));
+    std::swap(ctx->demon, ctx->demon_alt);
+    return ctx_to_buffer(ctx, home);
 }
 
 int ising_creutz_sweep(ising_ctx* ctx, uint64_t n, int reverse) {

@@ -48,3 +48,64 @@ def test_creutz_pairs_equal_oracle(b, o, L, hi, calls):
         assert np.array_equal(b.ising_copy_demons(ctx, L), d)
     finally:
         b.ising_destroy(ctx)
+
+
+@pytest.mark.parametrize("L,hi,calls", [(4104, 255, [4, -5]), (5000, 4, [-4, 6]), (8192, 3, [4, -4]), (8200, 255, [7]),
+                                        (10000, 3, [-4, 4]), (16384, 3, [4]), (16392, 3, [-4]), (20016, 4, [4])])
+def test_calls_of_several_pairs_equal_oracle(b, o, L, hi, calls):
+    """One to three launches of two sweeps, zero to three single sweeps."""
+    test_creutz_pairs_equal_oracle(b, o, L, hi, calls)
+
+
+@pytest.mark.parametrize("L,captured,eager", [(4104, "reverse", [-2]), (4104, "reverse", [3, -7]), (4104, "static", [6]),
+                                              (8192, "static", [2]), (8192, "static", [6, -2]), (8192, "reverse", [-6])])
+def test_captured_graphs_stay_valid(b, L, captured, eager):
+    """A graph of reversed Creutz sweeps or of static Metropolis sweeps holds
+    the addresses of the lattice and the demons: after eager Creutz calls a
+    replay goes on from where they ended."""
+    import torch
+    G.log(f"graph of {captured} sweeps after eager Creutz calls L={L} eager={eager}")
+    s, p = torch.cuda.Stream(), dict(J=1.0, h=0.0, T=2.3, seed=9)
+    c, r = b.ising_create(L, stream=s.cuda_stream, **p), b.ising_create(L, **p)
+    demons = W.random_demons(L, 5, 3)
+    try:
+        for ctx in (c, r):
+            b.ising_reserve(ctx, 256)
+        series = torch.zeros(4, dtype=torch.int64, device="cuda")
+        spins = b.ising_copy_spins(c, L)
+
+        def sweep(ctx):
+            if captured == "static":
+                b.ising_sweep_static(ctx, 2, series.data_ptr())
+            else:
+                b.ising_creutz_sweep(ctx, 2, reverse=True)
+
+        def restart(ctx):
+            b.ising_load_spins(ctx, spins, 0)
+            b.ising_creutz_init(ctx, demons)
+
+        b.ising_creutz_init(c, demons)
+        for n in (8, -8):  # every buffer that eager calls take is there
+            b.ising_creutz_sweep(c, abs(n), n < 0)
+        sweep(c)
+        restart(c)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            sweep(c)
+        for _ in range(3):
+            restart(c)
+            restart(r)
+            for ctx in (c, r):
+                for n in eager:
+                    b.ising_creutz_sweep(ctx, abs(n), n < 0)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            sweep(r)
+            torch.cuda.synchronize()
+            assert np.array_equal(b.ising_copy_spins(c, L), b.ising_copy_spins(r, L))
+            assert np.array_equal(b.ising_copy_demons(c, L), b.ising_copy_demons(r, L))
+    finally:
+        b.ising_destroy(c)
+        b.ising_destroy(r)
