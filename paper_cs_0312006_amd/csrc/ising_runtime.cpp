@@ -357,17 +357,24 @@ static size_t band_slot_words(uint32_t L, uint32_t G) {
 }
 
 // `words` tagged edge-row words for band launches, and their timeout mark (the
-// slots only grow; growing waits for the launches that may still use them).
+// slots only grow; growing waits for the launches that may still use them, and
+// where it fails the slots there were stay).
 static int ctx_band_slots(ising_ctx* ctx, size_t words) {
     if (words > ctx->band_words) {
-        if (ctx->band_words) HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-        if (ctx->band_pub) (void)hipFree(ctx->band_pub);
-        ctx->band_pub = nullptr;
-        ctx->band_words = 0;
-        if (hipMalloc(&ctx->band_pub, words * sizeof(uint64_t)) != hipSuccess) {
+        uint64_t* fresh = nullptr;
+        if (hipMalloc(&fresh, words * sizeof(uint64_t)) != hipSuccess) {
             (void)hipGetLastError();
             return ISING_ENOMEM;
         }
+        if (ctx->band_pub) {
+            const hipError_t e = hipStreamSynchronize(ctx->stream);
+            if (e != hipSuccess) {
+                (void)hipFree(fresh);
+                return ctx_fail(ctx, e, "band plan: edge slots");
+            }
+            (void)hipFree(ctx->band_pub);
+        }
+        ctx->band_pub = fresh;
         // fresh slots carry tag 0, below every tag a launch waits for
         HIP_TRY(ctx, hipMemsetAsync(ctx->band_pub, 0, words * sizeof(uint64_t), ctx->stream));
         ctx->band_base = 0;
@@ -389,20 +396,23 @@ static int ctx_band_slots(ising_ctx* ctx, size_t words) {
 // The band plan's partials for launches of kBandChunk sweeps (G pairs a
 // sweep), allocated on the first ising_sweep of a band plan (a context that
 // only runs in batches never needs them, and ising_sweep_static uses the
-// library's array instead).
+// library's array instead). On failure those there were stay.
 static int ctx_band_part(ising_ctx* ctx, uint32_t G) {
     if (ctx->band_part && ctx->band_part_cap >= G) return ISING_OK;
-    if (ctx->band_part) {
-        HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-        (void)hipFree(ctx->band_part);
-        ctx->band_part = nullptr;
-        ctx->band_part_cap = 0;
-    }
-    if (hipMalloc(&ctx->band_part, (size_t)kBandChunk * G * 2 * sizeof(int64_t)) != hipSuccess) {
+    int64_t* fresh = nullptr;
+    if (hipMalloc(&fresh, (size_t)kBandChunk * G * 2 * sizeof(int64_t)) != hipSuccess) {
         (void)hipGetLastError();
-        ctx->band_part = nullptr;
         return ISING_ENOMEM;
     }
+    if (ctx->band_part) {
+        const hipError_t e = hipStreamSynchronize(ctx->stream);
+        if (e != hipSuccess) {
+            (void)hipFree(fresh);
+            return ctx_fail(ctx, e, "band plan: partial sums");
+        }
+        (void)hipFree(ctx->band_part);
+    }
+    ctx->band_part = fresh;
     ctx->band_part_cap = G;
     return ISING_OK;
 }
@@ -527,6 +537,7 @@ static int ctx_band_tags(ising_ctx* ctx, uint32_t m) {
 static int sweep_bands(ising_ctx* ctx, uint64_t n, int64_t* ser, int64_t* part, uint32_t chunk, uint32_t rows,
                        uint32_t per_wave) {
     const uint32_t L = ctx->L, G = band_count(L, rows);
+    if (!ctx->band_pub || ctx->band_words < band_slot_words(L, G)) return ISING_ENOMEM;
     const Planes pl = ctx_planes(ctx);
     const uint32_t mode = bits_mode(ctx->table);
     BandArgs a{};

@@ -1,0 +1,32 @@
+"""The library's host side under failures that a GPU run cannot ask for, with
+its HIP calls served by host memory."""
+import pytest
+
+from tests import hip_host
+
+
+@pytest.mark.parametrize("L,plan", [(2048, "AUTO"), (96, "BANDS"), (1002, "AUTO")])
+def test_band_memory_stays_when_it_cannot_grow(tmp_path, L, plan):
+    """Creutz bands take more edge words than Metropolis bands. Where those
+    are not to be had the sweeps run without bands (or, where that takes a
+    second lattice, are refused), and the words and partial sums that the band
+    plan has are still there for its next launch."""
+    hip_host.run(tmp_path, f"""
+        c = b.ising_create({L}, flags=b.ISING_PLAN_{plan})
+        b.ising_creutz_init(c, None, 1)
+        b.ising_reserve(c, 64)
+        b.ising_sweep(c, 40)
+        assert h.cooperative == 1
+        live = h.live
+        h.fail_malloc = 0
+        try:
+            b.ising_creutz_sweep(c, 5)
+        except b.IsingError as e:
+            assert e.code == b.ISING_ENOMEM and {L} % 512 == 0
+        assert h.cooperative == 1 and h.live == live, (h.cooperative, live, h.live)
+        b.ising_sweep(c, 20)
+        assert h.cooperative == 2
+        h.fail_malloc = -1
+        b.ising_creutz_sweep(c, 5)
+        assert h.cooperative == 3 and h.live > live
+    """)
