@@ -1750,6 +1750,8 @@ int ising_demon_sum(ising_ctx* ctx, int64_t* out) {
     int64_t v = 0;
     HIP_TRY(ctx, hipMemcpyAsync(&v, ctx->scratch + 2, sizeof(v), hipMemcpyDeviceToHost, ctx->stream));
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+    rc = band_check(ctx);
+    if (rc != ISING_OK) return rc;
     *out = v;
     return ISING_OK;
 }
@@ -1765,7 +1767,7 @@ int ising_copy_demons(ising_ctx* ctx, uint8_t* host, size_t n) {
     HIP_TRY(ctx, launch_bytes_to_canonical(planes_of(ctx->demon, ctx->L), reinterpret_cast<uint8_t*>(ctx->canon),
                                            ctx->stream));
     HIP_TRY(ctx, copy_to_host(host, ctx->canon, N, ctx->stream));
-    return ISING_OK;
+    return band_check(ctx);
 }
 
 int ising_destroy(ising_ctx* ctx) {

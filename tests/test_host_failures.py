@@ -30,3 +30,25 @@ def test_band_memory_stays_when_it_cannot_grow(tmp_path, L, plan):
         b.ising_creutz_sweep(c, 5)
         assert h.cooperative == 3 and h.live > live
     """)
+
+
+@pytest.mark.parametrize("read", ["ising_copy_demons(c, 1024)", "ising_demon_sum(c)", "ising_copy_spins(c, 1024)",
+                                  "ising_observables(c)"])
+def test_an_edge_wait_that_gave_up_is_reported(tmp_path, read):
+    """A band launch of Creutz sweeps that marks a time-out leaves no valid
+    state: every read-back says so."""
+    hip_host.run(tmp_path, f"""
+        c = b.ising_create(1024)
+        b.ising_creutz_init(c, None, 1)
+        b.ising_creutz_sweep(c, 5)
+        b.{read}
+        h.mark = 1
+        b.ising_creutz_sweep(c, 5)
+        assert h.cooperative == 2
+        try:
+            b.{read}
+        except b.IsingError as e:
+            assert e.code == b.ISING_EDEVICE, e.code
+        else:
+            raise AssertionError("no error")
+    """)
