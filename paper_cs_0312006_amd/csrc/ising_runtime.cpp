@@ -215,6 +215,11 @@ static bool untuned_plan(uint32_t L, Plan* out) {
     return plan_for(L, ISING_PLAN_TWO_PASS, 0, 0, out);
 }
 
+static bool is_side_plan(uint32_t L, const Plan& p) {
+    Plan d;
+    return untuned_plan(L, &d) && d.kind == p.kind && d.cw == p.cw && d.rows == p.rows;
+}
+
 bool plan_for(uint32_t L, uint32_t kind, uint32_t cw, uint32_t rows, Plan* out) {
     Plan pl{};
     const bool words = (L % 8u) == 0u;
@@ -729,10 +734,7 @@ static int create_common(const ising_params* params, void* dev_buf, size_t bytes
     ctx->p = *params;
     ctx->L = params->L;
     ctx->plan = plan;
-    if ((params->flags & 0xffu) == ISING_PLAN_AUTO) {
-        std::lock_guard<std::mutex> g(g_tuned_mu);
-        ctx->plan_by_side = g_tuned.find(params->L) == g_tuned.end();
-    }
+    ctx->plan_by_side = (params->flags & 0xffu) == ISING_PLAN_AUTO && is_side_plan(params->L, plan);
     build_accept_table(params->J, params->h, params->T, &ctx->table, &ctx->exact);
     hostcopy_retain();
     if (hipGetDevice(&ctx->device) != hipSuccess) {
@@ -832,10 +834,10 @@ int ising_reserve(ising_ctx* ctx, uint64_t sweeps) {
 }
 
 // Whether sweeps of this context run over wave tiles of any row length
-// (ising_tiles.hip). They do under the plan the side has by default (any
-// other plan that the caller sets or tunes runs as it is; ising_tune times
-// the default with its tiles) where that is slower; us a sweep, default plan
-// against tiles:
+// (ising_tiles.hip). They do under the plan that AUTO gives the side (a plan
+// that the caller sets, or that ising_tune prefers to it, runs as it is;
+// ising_tune times the side's with its tiles) where that is slower; us a sweep,
+// default plan against tiles:
 //   the band plan in a field (general thresholds) beyond the row bands: 4104^2
 //     27.2 and 19.5, 8192^2 51.0 and 46.2, 16384^2 182 and 156. Without a field
 //     the bands by bits are faster: 4104^2 19.5 and 19.4, 8192^2 36.8 and 44,
@@ -845,14 +847,10 @@ int ising_reserve(ising_ctx* ctx, uint64_t sweeps) {
 //     level (16416^2 170 and 172)
 static bool tiles_serve(const ising_ctx* ctx) {
     const uint32_t L = ctx->L;
-    if (L % 8u != 0u || L <= 4096u) return false;
-    if (ctx->plan.kind == ISING_PLAN_BANDS) {
-        if (bits_mode(ctx->table) != 3u || row_bands_serve(L, band_count(L, ctx->plan.rows), false)) return false;
-    } else if (ctx->plan.kind != ISING_PLAN_TWO_PASS || band_words(L) <= kBandMaxWr) {
-        return false;
-    }
-    Plan d;
-    return untuned_plan(L, &d) && d.kind == ctx->plan.kind && d.cw == ctx->plan.cw && d.rows == ctx->plan.rows;
+    if (!ctx->plan_by_side || L % 8u != 0u || L <= 4096u) return false;
+    if (ctx->plan.kind == ISING_PLAN_BANDS)
+        return bits_mode(ctx->table) == 3u && !row_bands_serve(L, band_count(L, ctx->plan.rows), false);
+    return ctx->plan.kind == ISING_PLAN_TWO_PASS && band_words(L) > kBandMaxWr;
 }
 
 // Sweeps under a plan in place leave the lattice in the buffer they found it
@@ -1445,20 +1443,19 @@ int ising_tune(ising_ctx* ctx, uint32_t trial_sweeps) {
     float best_ms = 0.f;
     Plan best = ctx->plan;
     bool have = false;
-    // the default plan for this side is timed first and kept unless beaten
-    Plan dflt;
+    // the default plan for this side (AUTO's, untuned) is timed first, as AUTO
+    // runs it, and kept unless beaten
     {
         std::lock_guard<std::mutex> g(g_tuned_mu);
-        g_tuned.erase(L);  // the default is the untuned AUTO choice
+        g_tuned.erase(L);
     }
-    if (plan_for(L, ISING_PLAN_AUTO, 0, 0, &dflt)) {
-        for (size_t k = 0; k < cands.size(); ++k) {
-            if (cands[k].kind == dflt.kind && cands[k].cw == dflt.cw && cands[k].rows == dflt.rows) {
-                std::swap(cands[0], cands[k]);
-                break;
-            }
+    for (size_t k = 0; k < cands.size(); ++k) {
+        if (is_side_plan(L, cands[k])) {
+            std::swap(cands[0], cands[k]);
+            break;
         }
     }
+    const bool side_first = is_side_plan(L, cands[0]);
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) rc = ISING_EDEVICE;
     // kTuneRounds interleaved rounds over the candidates; each keeps its
     // fastest round, so a slow outlier (clock ramp, a neighbour's work)
@@ -1468,6 +1465,7 @@ int ising_tune(ising_ctx* ctx, uint32_t trial_sweeps) {
         for (size_t k = 0; rc == ISING_OK && k < cands.size(); ++k) {
             ctx_drop_graphs(tmp);  // graphs captured for the previous candidate
             tmp->plan = cands[k];
+            tmp->plan_by_side = k == 0 && side_first;
             rc = ctx_prepare_plan(tmp);
             if (rc != ISING_OK) break;
             if (hipMemcpyAsync(tmp->buf[tmp->cur], ctx->buf[ctx->cur], N, hipMemcpyDeviceToDevice, ctx->stream) !=
@@ -1512,7 +1510,7 @@ int ising_tune(ising_ctx* ctx, uint32_t trial_sweeps) {
         ctx->plan = old;
         return rc;
     }
-    ctx->plan_by_side = false;
+    ctx->plan_by_side = is_side_plan(L, best);
     std::lock_guard<std::mutex> g(g_tuned_mu);
     g_tuned[L] = best;
     return ISING_OK;

@@ -1,0 +1,60 @@
+"""Which kernels a call goes to, on the host side alone: the library's HIP
+calls are served by host memory, its launches counted."""
+import pytest
+
+from tests import hip_host
+
+
+@pytest.mark.parametrize("L,h", [(4104, 0.1), (16392, 0.0)])
+def test_a_forced_plan_runs_as_it_is(tmp_path, L, h):
+    """Beyond the row bands AUTO sweeps between two buffers (wave tiles); a
+    plan that the caller forces, at creation or later, runs in its own."""
+    hip_host.run(tmp_path, f"""
+        L = {L}
+        plan = b.ISING_PLAN_BANDS if L <= 16384 else b.ISING_PLAN_TWO_PASS
+        def sweep(c):
+            b.ising_reserve(c, 1024)
+            b.ising_sweep(c, 1)
+            n, live = h.cooperative, h.live
+            b.ising_sweep(c, 3)
+            return h.cooperative - n, h.live - live >= L * L
+        banded = 1 if L <= 16384 else 0
+        auto = b.ising_create(L, h={h})
+        assert b.ising_plan_info(auto)[0] == plan
+        assert sweep(auto) == (0, True)
+        assert sweep(b.ising_create(L, h={h}, flags=plan)) == (banded, False)
+        c = b.ising_create(L, h={h})
+        b.ising_plan_set(c, plan)
+        assert sweep(c) == (banded, False)
+    """)
+
+
+@pytest.mark.parametrize("trial", [4, 20])
+def test_a_tuned_default_runs_as_before(tmp_path, trial):
+    """The plan of the side, when nothing beats it, goes on being run with its
+    wave tiles, on the tuned context and on later ones."""
+    hip_host.run(tmp_path, f"""
+        c = b.ising_create(4104, h=0.1)
+        info = b.ising_plan_info(c)
+        b.ising_tune(c, {trial})
+        assert b.ising_plan_info(c) == info
+        for ctx in (c, b.ising_create(4104, h=0.1)):
+            n = h.cooperative
+            b.ising_sweep(ctx, 3)
+            assert h.cooperative == n
+    """)
+
+
+@pytest.mark.parametrize("L", [96, 136, 184])
+def test_a_tuned_default_is_captured_as_before(tmp_path, L):
+    """ising_sweep of these sides can be captured; tuning that keeps the plan
+    changes nothing."""
+    hip_host.run(tmp_path, f"""
+        c = b.ising_create({L})
+        b.ising_tune(c, 4)
+        for ctx in (c, b.ising_create({L})):
+            b.ising_reserve(ctx, 8)
+            h.capturing = 1
+            b.ising_sweep(ctx, 3)
+            h.capturing = 0
+    """)
