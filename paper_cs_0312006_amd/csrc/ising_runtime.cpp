@@ -88,8 +88,9 @@ constexpr float kTuneMargin = 0.03f;
 // Band plan: sides it serves by default, and sweeps per launch (the
 // partials of a launch are bands x sweeps pairs).
 constexpr uint32_t kBandMinDefaultL = 96;
-// Short calls of small band-plan lattices run in one workgroup: a cooperative
-// launch and the sum of its partials cost about 10 us more than its launch.
+// Short calls of small lattices that run on bands by AUTO's choice (a forced
+// plan runs as it is, and so do the shapes that ising_tune compares) take one
+// workgroup: a cooperative launch and the sum of its partials cost about 10 us more than its launch.
 // At 96 to 128 the bands win from about 20 sweeps (a call of 10: 49 against
 // 56 us; 1.9 against 1.4 us a sweep), up to 184 from three (one sweep: 35
 // against 44 us; three: 47 each), above from the first.
@@ -913,8 +914,8 @@ int ising_sweep(ising_ctx* ctx, uint64_t n) {
     rc = ctx_reserve_series(ctx, n);
     if (rc != ISING_OK) return rc;
     ++ctx->gen;
-    if (ctx->plan.kind == ISING_PLAN_RESIDENT ||
-        (ctx->plan.kind == ISING_PLAN_BANDS && (captured || short_band_call(ctx->L, n)))) {
+    if (ctx->plan.kind == ISING_PLAN_RESIDENT || captured ||
+        (ctx->plan.kind == ISING_PLAN_BANDS && ctx->plan_by_side && short_band_call(ctx->L, n))) {
         // one workgroup runs every sweep from local memory (bytes: a lone
         // lattice's latency, not the chip's throughput, sets the time)
         BatchItem it;

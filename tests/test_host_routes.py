@@ -58,3 +58,24 @@ def test_a_tuned_default_is_captured_as_before(tmp_path, L):
             b.ising_sweep(ctx, 3)
             h.capturing = 0
     """)
+
+
+@pytest.mark.parametrize("L", [136, 184])
+def test_short_calls_of_a_forced_band_plan_run_on_bands(tmp_path, L):
+    """Only AUTO's choice gives short calls of small sides to one workgroup;
+    ising_tune's band shapes are each timed on the band kernel."""
+    hip_host.run(tmp_path, f"""
+        def launches(c, n):
+            k = h.cooperative
+            b.ising_sweep(c, n)
+            return h.cooperative - k
+        auto, forced = b.ising_create({L}), b.ising_create({L}, flags=b.ISING_PLAN_BANDS)
+        assert launches(auto, 1) == 0 and launches(auto, 2) == 0 and launches(auto, 30) == 1
+        assert launches(forced, 1) == 1 and launches(forced, 2) == 1
+        b.ising_plan_set(auto, b.ISING_PLAN_BANDS, 1, 8)
+        assert launches(auto, 1) == 1
+        k = h.cooperative
+        b.ising_tune(b.ising_create({L}), 2)
+        # heights 4 (the default: AUTO's), 2, 8, 16 and 32, three rounds, a warm-up of one sweep each
+        assert h.cooperative - k == 3 * 4 * 2, h.cooperative - k
+    """)
