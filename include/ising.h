@@ -63,8 +63,8 @@ extern "C" {
 #define ISING_MAX_L 65536u     /* counter word 0 holds site/8: L*L/8 must fit 32 bits */
 
 /* Plan selection (ising_params.flags, low byte). AUTO picks per lattice side:
- * the workgroup-resident kernel for small sides, the band-resident plan for
- * sides 96 to 16384 (about one band of rows per compute unit), the fused
+ * the workgroup-resident kernel for sides up to 128, the band-resident plan for
+ * sides 136 to 16384 (about one band of rows per compute unit), the fused
  * one-pass sweep by wave tiles for larger sides whose rows are whole tiles,
  * the two-pass plan otherwise. Under those defaults, lattices in a field
  * beyond 4096 and sides of the two-pass plan beyond 16384 are swept in one
@@ -228,7 +228,7 @@ int ising_load_spins(ising_ctx* ctx, const int8_t* host, size_t n, uint64_t t);
  * predicted slower, graph replays of passes that spread every lattice over
  * the whole GPU. The descriptors are staged through pinned host
  * memory by one copy kernel. A batch with a single lattice to sweep whose
- * side the band-resident plan serves by default (96 to 16384) runs on that
+ * side is from 96 to 16384 (and fits the band-resident plan) runs on that
  * plan instead, on the context's stream ordered after `stream`'s earlier
  * work and before its later work (neither batch plan can spread one lattice
  * over the chip). Lattices may differ in L, J, h, T and seed;

@@ -77,9 +77,14 @@ static bool valid_params(const ising_params* p) {
 static std::mutex g_tuned_mu;
 static std::map<uint32_t, Plan> g_tuned;
 
-// Sides up to this run all their sweeps inside one workgroup by default (88^2:
-// 1.13 us a sweep against 1.38 on bands, 96^2 1.9 against 1.42).
-constexpr uint32_t kResidentMaxL = 88;
+// Sides up to this run all their sweeps inside one workgroup by default. A lone
+// lattice would be faster on bands from 96 up (88^2 1.10 us a sweep against 1.37,
+// 96^2 to 128^2 1.88 against 1.40), but band launches are cooperative, and those
+// of different streams run one after another, where workgroups share the chip:
+// 16 contexts of 96^2 or 128^2 with streams of their own take 22.0 us for a
+// sweep of each on bands, 36 in calls of 20 sweeps, and 9.5 and 10.6 in
+// workgroups.
+constexpr uint32_t kResidentMaxL = 128;
 // Fused tiles wanted per launch (one wave each) before a taller/wider tile is used.
 constexpr uint32_t kFusedMinTiles = 16384;
 // The autotuner replaces the default plan only when a candidate is faster
@@ -87,16 +92,17 @@ constexpr uint32_t kFusedMinTiles = 16384;
 constexpr float kTuneMargin = 0.03f;
 // Band plan: sides it serves by default, and sweeps per launch (the
 // partials of a launch are bands x sweeps pairs).
-constexpr uint32_t kBandMinDefaultL = 96;
-// Short calls of small lattices that run on bands by AUTO's choice (a forced
-// plan runs as it is, and so do the shapes that ising_tune compares) take one
-// workgroup: a cooperative launch and the sum of its partials cost about 10 us more than its launch.
-// At 96 to 128 the bands win from about 20 sweeps (a call of 10: 49 against
-// 56 us; 1.9 against 1.4 us a sweep), up to 184 from three (one sweep: 35
-// against 44 us; three: 47 each), above from the first.
-static bool short_band_call(uint32_t L, uint64_t n) {
-    return L >= kBandMinDefaultL && ((L <= 128u && n < 20u) || (L <= 184u && n <= 2u));
-}
+constexpr uint32_t kBandMinDefaultL = 136;
+// A batch with one lattice to sweep takes bands from this side (96^2: 30 us for
+// a sweep and 298 for 200, the resident batch 96 and 440; batches are launched
+// one after another in any case).
+constexpr uint32_t kLoneBandMinL = 96;
+// Calls of one or two sweeps of the smallest lattices that run on bands by
+// AUTO's choice (a forced plan runs as it is, and so do the shapes that
+// ising_tune compares) take one workgroup: a cooperative launch and the sum of
+// its partials cost about 10 us more than its launch (136^2: one sweep 19 us
+// against 28, two 23 and 30, three 31 each; 184^2 22, 29 and 31).
+static bool short_band_call(uint32_t L, uint64_t n) { return L <= 184u && n <= 2u; }
 constexpr uint32_t kBandChunk = ISING_BAND_SWEEPS_PER_LAUNCH;
 constexpr uint32_t kTuneRounds = 3;
 
@@ -893,23 +899,19 @@ static int sweep_tiles(ising_ctx* ctx, uint64_t n, int64_t* ser, bool* served) {
     return ctx_to_buffer(ctx, home);
 }
 
-// A captured stream, or a caller of ising_sweep_static with several contexts
-// in flight, cannot use a band launch (its tags advance on the host; its
-// partials go to the array that calls share). The smallest sides that run
-// bands by default were served there by plans without those limits, and are
-// by one workgroup.
-static bool one_workgroup(const ising_ctx* ctx, uint32_t limit) {
-    return ctx->plan.kind == ISING_PLAN_BANDS && ctx->plan_by_side && ctx->L <= limit;
+// A captured stream cannot take a band launch (its tags advance on the host).
+// The smallest sides that run bands by default are swept there by one
+// workgroup.
+static bool captured_in_one_workgroup(const ising_ctx* ctx) {
+    return ctx->plan.kind == ISING_PLAN_BANDS && ctx->plan_by_side && ctx->L <= 184u;
 }
-constexpr uint32_t kCaptureMaxL = 184;    // ising_sweep under capture, and static sweeps
-constexpr uint32_t kNoScratchMaxL = 128;  // static sweeps that use no shared array
 
 int ising_sweep(ising_ctx* ctx, uint64_t n) {
     int rc = ctx_enter(ctx);
     if (rc != ISING_OK) return rc;
     if (n == 0) return ISING_OK;
     const bool captured = ctx->plan.kind == ISING_PLAN_BANDS && stream_capturing(ctx->stream);
-    if (captured && !one_workgroup(ctx, kCaptureMaxL)) return ISING_EUNSUPPORTED;
+    if (captured && !captured_in_one_workgroup(ctx)) return ISING_EUNSUPPORTED;
     if (ctx->t + n > ((uint64_t)1 << 32)) return ISING_ERANGE;
     rc = ctx_reserve_series(ctx, n);
     if (rc != ISING_OK) return rc;
@@ -990,7 +992,7 @@ int ising_sweep_static(ising_ctx* ctx, uint64_t n, int64_t* series_dev) {
     if (ctx->plan.kind == ISING_PLAN_TWO_PASS) pairs = two_pass_blocks(ctx_planes(ctx), ctx->plan.cw);
     // under capture the band plan's sweeps run as two-pass launches
     const bool bands_as_two_pass = ctx->plan.kind == ISING_PLAN_BANDS && stream_capturing(ctx->stream);
-    const bool one_group = one_workgroup(ctx, bands_as_two_pass ? kCaptureMaxL : kNoScratchMaxL);
+    const bool one_group = bands_as_two_pass && captured_in_one_workgroup(ctx);
     if (ctx->plan.kind == ISING_PLAN_BANDS && !one_group)
         pairs = bands_as_two_pass ? two_pass_blocks(ctx_planes(ctx), 1) : band_count(ctx->L, ctx->plan.rows);
     if (pairs > ISING_STATIC_SCRATCH_PAIRS) return ISING_ERANGE;
@@ -1076,11 +1078,10 @@ static int lone_band_batch(ising_ctx* ctx, uint64_t n, hipStream_t s) {
     return ISING_OK;
 }
 
-// Whether a batch of one lattice with sweeps goes to lone_band_batch: the
-// sides where the band plan is the single-lattice default.
+// Whether a batch of one lattice with sweeps goes to lone_band_batch.
 static bool lone_band_fits(const ising_ctx* c) {
     Plan bp;
-    return c->L >= kBandMinDefaultL && plan_for(c->L, ISING_PLAN_BANDS, 0, 0, &bp);
+    return c->L >= kLoneBandMinL && plan_for(c->L, ISING_PLAN_BANDS, 0, 0, &bp);
 }
 
 int ising_sweep_batch_plan(ising_ctx* const* ctxs, const uint64_t* n_sweeps, size_t count, void* stream,

@@ -79,3 +79,16 @@ def test_short_calls_of_a_forced_band_plan_run_on_bands(tmp_path, L):
         # heights 4 (the default: AUTO's), 2, 8, 16 and 32, three rounds, a warm-up of one sweep each
         assert h.cooperative - k == 3 * 4 * 2, h.cooperative - k
     """)
+
+
+@pytest.mark.parametrize("L", [96, 104, 128])
+def test_small_lattices_of_several_streams_share_the_chip(tmp_path, L):
+    """Sweeps of default contexts of these sides are single workgroups, which
+    run side by side on several streams; band launches are cooperative, one
+    at a time."""
+    hip_host.run(tmp_path, f"""
+        for c in [b.ising_create({L}) for _ in range(4)]:
+            for n in (1, 20, 600):
+                b.ising_sweep(c, n)
+        assert h.cooperative == 0 and h.launches >= 12
+    """)
