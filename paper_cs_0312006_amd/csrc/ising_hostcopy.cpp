@@ -23,7 +23,6 @@
 #include <atomic>
 #include <mutex>
 #include <new>
-#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -148,8 +147,10 @@ struct Ring {
         slot_chunk[k].store(c, std::memory_order_release);
         return e == hipSuccess;
     }
-    void work() {
-        if (hipSetDevice(device) != hipSuccess) return;  // the calling thread's device is set: it does it all
+    // `helper`: not the calling thread, whose device is set and which moves
+    // whatever chunks the helpers do not take.
+    void work(bool helper) {
+        if (helper && hipSetDevice(device) != hipSuccess) return;
         for (;;) {
             const uint64_t c = next.fetch_add(1, std::memory_order_relaxed);
             if (c >= chunks || error.load(std::memory_order_relaxed) != (int)hipSuccess) return;
@@ -211,10 +212,10 @@ hipError_t copy_to_host(void* dst, const void* src, size_t bytes, hipStream_t s)
     uint32_t n = 0;
     const uint32_t want = ok ? (uint32_t)std::min<uint64_t>(host_threads(), r.chunks) - 1u : 0u;
     try {
-        for (; n < want; ++n) extra[n] = std::thread([&r] { r.work(); });
-    } catch (const std::system_error&) {  // fewer threads
+        for (; n < want; ++n) extra[n] = std::thread([&r] { r.work(true); });
+    } catch (...) {  // no thread, or no memory for one: fewer threads
     }
-    if (ok) r.work();
+    if (ok) r.work(false);
     for (uint32_t k = 0; k < n; ++k) extra[k].join();
     // nothing may still be on its way into the stage when it is given back
     const hipError_t e = hipStreamSynchronize(s);

@@ -21,14 +21,19 @@ extern "C" {
 // Counters and switches, read and set by the tests.
 long host_fail_malloc = -1;       // this many further device allocations succeed (-1: all)
 long host_fail_set_device = -1;   // as above, hipSetDevice
+long host_fail_new = -1;          // as above, operator new
 long host_live = 0;               // bytes of device memory allocated
 long host_mallocs = 0, host_launches = 0, host_cooperative = 0, host_copies = 0;
 long host_capturing = 0;           // every stream is being captured
 long host_mark = 0;                // cooperative launches set the 4-byte words of pinned memory (time-out marks)
 
 static bool fails(long* left) {
-    std::lock_guard<std::mutex> g(mu);
-    return *left >= 0 && (*left)-- <= 0 && (*left = 0, true);
+    static std::mutex own;
+    std::lock_guard<std::mutex> g(own);
+    if (*left < 0) return false;
+    if (*left == 0) return true;
+    --*left;
+    return false;
 }
 
 int hipMalloc(void** p, size_t n) {
@@ -126,3 +131,11 @@ int hipLaunchCooperativeKernel(const void*, Dim, Dim, void**, unsigned, void*) {
 }
 
 }  // extern "C"
+
+void* operator new(size_t n) {
+    if (fails(&host_fail_new)) throw std::bad_alloc();
+    if (void* p = malloc(n ? n : 1)) return p;
+    throw std::bad_alloc();
+}
+void operator delete(void* p) noexcept { free(p); }
+void operator delete(void* p, size_t) noexcept { free(p); }

@@ -4,6 +4,7 @@ counters and switches of the host calls."""
 import os
 import subprocess
 import sys
+import tempfile
 import textwrap
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -20,10 +21,21 @@ from paper_cs_0312006_amd import binding as b
 """
 
 
-def run(tmp_path, snippet):
-    so = str(tmp_path / "hip_host.so")
-    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", os.path.join(ROOT, "tests", "hip_host.cpp"),
-                    "-o", so, "-lpthread"], check=True)
-    r = subprocess.run([sys.executable, "-c", HEAD + textwrap.dedent(snippet), ROOT, so], capture_output=True,
+_built = []
+
+
+def _library():
+    """Built once a process, in a folder that goes with it."""
+    if not _built:
+        folder = tempfile.TemporaryDirectory()
+        so = os.path.join(folder.name, "hip_host.so")
+        subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", os.path.join(ROOT, "tests", "hip_host.cpp"),
+                        "-o", so, "-lpthread"], check=True)
+        _built.append((folder, so))
+    return _built[0][1]
+
+
+def run(snippet):
+    r = subprocess.run([sys.executable, "-c", HEAD + textwrap.dedent(snippet), ROOT, _library()], capture_output=True,
                        text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr

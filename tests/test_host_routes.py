@@ -6,10 +6,10 @@ from tests import hip_host
 
 
 @pytest.mark.parametrize("L,h", [(4104, 0.1), (16392, 0.0)])
-def test_a_forced_plan_runs_as_it_is(tmp_path, L, h):
+def test_a_forced_plan_runs_as_it_is(L, h):
     """Beyond the row bands AUTO sweeps between two buffers (wave tiles); a
     plan that the caller forces, at creation or later, runs in its own."""
-    hip_host.run(tmp_path, f"""
+    hip_host.run(f"""
         L = {L}
         plan = b.ISING_PLAN_BANDS if L <= 16384 else b.ISING_PLAN_TWO_PASS
         def sweep(c):
@@ -30,10 +30,10 @@ def test_a_forced_plan_runs_as_it_is(tmp_path, L, h):
 
 
 @pytest.mark.parametrize("trial", [4, 20])
-def test_a_tuned_default_runs_as_before(tmp_path, trial):
+def test_a_tuned_default_runs_as_before(trial):
     """The plan of the side, when nothing beats it, goes on being run with its
     wave tiles, on the tuned context and on later ones."""
-    hip_host.run(tmp_path, f"""
+    hip_host.run(f"""
         c = b.ising_create(4104, h=0.1)
         info = b.ising_plan_info(c)
         b.ising_tune(c, {trial})
@@ -46,10 +46,10 @@ def test_a_tuned_default_runs_as_before(tmp_path, trial):
 
 
 @pytest.mark.parametrize("L", [96, 136, 184])
-def test_a_tuned_default_is_captured_as_before(tmp_path, L):
+def test_a_tuned_default_is_captured_as_before(L):
     """ising_sweep of these sides can be captured; tuning that keeps the plan
     changes nothing."""
-    hip_host.run(tmp_path, f"""
+    hip_host.run(f"""
         c = b.ising_create({L})
         b.ising_tune(c, 4)
         for ctx in (c, b.ising_create({L})):
@@ -61,10 +61,10 @@ def test_a_tuned_default_is_captured_as_before(tmp_path, L):
 
 
 @pytest.mark.parametrize("L", [136, 184])
-def test_short_calls_of_a_forced_band_plan_run_on_bands(tmp_path, L):
+def test_short_calls_of_a_forced_band_plan_run_on_bands(L):
     """Only AUTO's choice gives short calls of small sides to one workgroup;
     ising_tune's band shapes are each timed on the band kernel."""
-    hip_host.run(tmp_path, f"""
+    hip_host.run(f"""
         def launches(c, n):
             k = h.cooperative
             b.ising_sweep(c, n)
@@ -82,11 +82,11 @@ def test_short_calls_of_a_forced_band_plan_run_on_bands(tmp_path, L):
 
 
 @pytest.mark.parametrize("L", [96, 104, 128])
-def test_small_lattices_of_several_streams_share_the_chip(tmp_path, L):
+def test_small_lattices_of_several_streams_share_the_chip(L):
     """Sweeps of default contexts of these sides are single workgroups, which
     run side by side on several streams; band launches are cooperative, one
     at a time."""
-    hip_host.run(tmp_path, f"""
+    hip_host.run(f"""
         for c in [b.ising_create({L}) for _ in range(4)]:
             for n in (1, 20, 600):
                 b.ising_sweep(c, n)
