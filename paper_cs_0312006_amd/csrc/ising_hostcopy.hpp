@@ -16,7 +16,7 @@ void hostcopy_release();
 
 // Copy `bytes` from device memory src (on the current device) to host memory
 // dst after the earlier work of stream s, and wait for it. Safe to call from
-// several threads. dst need not be pinned.
+// several threads. dst need not be pinned; where it is, the copy is direct.
 hipError_t copy_to_host(void* dst, const void* src, size_t bytes, hipStream_t s);
 
 }  // namespace ising

@@ -68,6 +68,14 @@ int hipHostFree(void* p) {
     return kSuccess;
 }
 int hipHostGetDevicePointer(void** d, void* h, unsigned) { return *d = h, kSuccess; }
+int hipPointerGetAttributes(int* type, const void* p) {  // the first field
+    std::lock_guard<std::mutex> g(mu);
+    auto it = host_mem.upper_bound(const_cast<void*>(p));
+    if (it == host_mem.begin()) return kInvalidValue;
+    --it;
+    if ((const char*)p >= (const char*)it->first + it->second) return kInvalidValue;
+    return *type = 1, kSuccess;
+}
 int hipMemcpyAsync(void* d, const void* s, size_t n, int, void*) {
     ++host_copies;
     memcpy(d, s, n);

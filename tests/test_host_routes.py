@@ -92,3 +92,21 @@ def test_small_lattices_of_several_streams_share_the_chip(L):
                 b.ising_sweep(c, n)
         assert h.cooperative == 0 and h.launches >= 12
     """)
+
+
+@pytest.mark.parametrize("L", [4096, 6000])
+def test_read_backs_into_pinned_memory_are_one_copy(L):
+    """A large lattice or its demons go straight into pinned memory, and
+    through the ring of chunks into any other."""
+    hip_host.run(f"""
+        N = {L} * {L}
+        c = b.ising_create({L})
+        b.ising_creutz_init(c, None, 1)
+        pinned, pageable = ctypes.c_void_p(), np.empty(N, dtype=np.int8)
+        assert lib.hipHostMalloc(ctypes.byref(pinned), ctypes.c_size_t(N), 0) == 0
+        for read in (b.lib().ising_copy_spins, b.lib().ising_copy_demons):
+            for dst, copies in ((pinned.value, 1), (pageable.ctypes.data, -(-N // (2 << 20)))):
+                n = h.copies
+                assert read(c, dst, N) == 0
+                assert h.copies - n == copies, (h.copies - n, copies)
+    """)
