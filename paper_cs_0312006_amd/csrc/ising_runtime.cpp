@@ -1575,6 +1575,9 @@ static int creutz_fused_prepare(ising_ctx* ctx, uint32_t cw, uint32_t rows) {
     const uint32_t need = fused_tiles(ctx->L, cw, rows);
     return grow_parts(ctx->cfpart, &ctx->cfpart_cap, need);
 }
+static bool creutz_fused_prepared(const ising_ctx* ctx, uint32_t cw, uint32_t rows) {
+    return ctx->buf[1] && ctx->demon_alt && ctx->cfpart_cap >= fused_tiles(ctx->L, cw, rows);
+}
 
 // n fused Creutz sweeps; series slots ser[0 .. 2n).
 static int creutz_sweep_fused(ising_ctx* ctx, uint64_t n, uint32_t cw, uint32_t rows, int64_t* ser) {
@@ -1660,7 +1663,9 @@ static int creutz_sweep_pairs(ising_ctx* ctx, uint64_t n, bool reverse, int64_t*
     HIP_TRY(ctx, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device));
     CreutzPairShape shape;
     if (!creutz_pairs_shape(L, (uint32_t)cus, &shape)) return ISING_OK;
-    int rc = creutz_second_buffers(ctx);
+    // with the partials of the single sweeps, which calls captured later take
+    uint32_t cw = 0, rows = 0;
+    int rc = default_fused(L, &cw, &rows) ? creutz_fused_prepare(ctx, cw, rows) : creutz_second_buffers(ctx);
     if (rc == ISING_OK) rc = ctx_band_part(ctx, shape.bands);
     if (rc == ISING_ENOMEM) return ISING_OK;
     if (rc != ISING_OK) return rc;
@@ -1714,7 +1719,10 @@ int ising_creutz_sweep(ising_ctx* ctx, uint64_t n, int reverse) {
     n = left;
     if (n == 0) return ISING_OK;
     uint32_t cw = 0, rows = 0;
-    if (!reverse && ctx->L % 8u == 0u && default_fused(ctx->L, &cw, &rows)) {
+    // A captured stream may not allocate: without the buffers (bands take most
+    // calls, and need none) its sweeps run in place.
+    if (!reverse && ctx->L % 8u == 0u && default_fused(ctx->L, &cw, &rows) &&
+        (creutz_fused_prepared(ctx, cw, rows) || !stream_capturing(ctx->stream))) {
         rc = creutz_fused_prepare(ctx, cw, rows);
         if (rc != ISING_OK) return rc;
         rc = creutz_sweep_fused(ctx, n, cw, rows, ser);

@@ -109,3 +109,40 @@ def test_captured_graphs_stay_valid(b, L, captured, eager):
     finally:
         b.ising_destroy(c)
         b.ising_destroy(r)
+
+
+@pytest.mark.parametrize("L,eager", [(512, [40]), (1024, [5, -5]), (8192, [4])])
+def test_forward_sweeps_are_captured_after_eager_ones(b, L, eager):
+    """Sides with wave tiles, whose eager calls run on bands or by pairs: a
+    forward call is captured without allocating, and replays like an eager
+    one."""
+    import torch
+    G.log(f"captured forward Creutz sweeps L={L}")
+    s, n, p = torch.cuda.Stream(), 2, dict(J=1.0, h=0.0, T=2.3, seed=9)
+    c, r = b.ising_create(L, stream=s.cuda_stream, **p), b.ising_create(L, **p)
+    demons = W.random_demons(L, 5, 3)
+    try:
+        spins = b.ising_copy_spins(c, L)
+        for ctx in (c, r):
+            b.ising_creutz_init(ctx, demons)
+            b.ising_reserve(ctx, 256)
+            for k in eager:
+                b.ising_creutz_sweep(ctx, abs(k), k < 0)
+            b.ising_load_spins(ctx, spins, 0)
+            b.ising_creutz_init(ctx, demons)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            b.ising_creutz_sweep(c, n)
+        b.ising_creutz_sweep(r, n)
+        for _ in range(3):
+            b.ising_load_spins(c, spins, 0)
+            b.ising_creutz_init(c, demons)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(b.ising_copy_spins(c, L), b.ising_copy_spins(r, L))
+            assert np.array_equal(b.ising_copy_demons(c, L), b.ising_copy_demons(r, L))
+    finally:
+        b.ising_destroy(c)
+        b.ising_destroy(r)
