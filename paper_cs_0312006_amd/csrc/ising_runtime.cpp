@@ -682,6 +682,9 @@ static int sweep_replays(ising_ctx* ctx, uint64_t n, uint64_t* left) {
     *left = n;
     const uint64_t reps = n / kGraphSweeps;
     if (reps == 0 || ctx->plan.kind != ISING_PLAN_TWO_PASS) return ISING_OK;
+    // a captured stream takes direct launches: building a graph would allocate,
+    // and the replay of one is not recorded as the sweeps it runs
+    if (stream_capturing(ctx->stream)) return ISING_OK;
     if (ctx->gexec && ctx->gcur != (uint32_t)ctx->cur) ctx_drop_graphs(ctx);  // a fused batch or Creutz sweep moved the lattice
     if (!ctx->gexec) {
         const int rc = ctx_build_graph(ctx);

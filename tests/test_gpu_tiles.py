@@ -161,3 +161,37 @@ def test_small_default_sides_are_captured_in_one_workgroup(b, L):
     finally:
         b.ising_destroy(c)
         b.ising_destroy(r)
+
+
+@pytest.mark.parametrize("L,flags,eager,n", [(16392, 0, 20, 16), (16392, 0, 3, 35), (1024, 1, 20, 16), (1024, 1, 3, 35)])
+def test_two_pass_sweeps_are_captured_after_eager_ones(b, L, flags, eager, n):
+    """Beyond 16384 eager sweeps run over tiles, and those of a two-pass plan
+    (flags 1) as replays of a graph of its own; a captured call of any length
+    runs as two-pass launches and replays like an eager one."""
+    import torch
+    G.log(f"captured sweeps of a two-pass side L={L} n={n}")
+    s = torch.cuda.Stream()
+    c = b.ising_create(L, T=2.3, seed=5, flags=flags, stream=s.cuda_stream)
+    r = b.ising_create(L, T=2.3, seed=5, flags=flags)
+    try:
+        b.ising_reserve(c, 512)
+        b.ising_sweep(c, eager)
+        start = b.ising_copy_spins(c, L)
+        b.ising_load_spins(c, start, 0)
+        b.ising_load_spins(r, start, 0)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            b.ising_sweep(c, n)
+        b.ising_sweep(r, n)
+        _, B, M = b.ising_observables(r, b.ISING_OBS_SERIES)
+        want = b.ising_copy_spins(r, L)
+        for _ in range(3):
+            b.ising_load_spins(c, start, 0)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(b.ising_copy_spins(c, L), want)
+    finally:
+        b.ising_destroy(c)
+        b.ising_destroy(r)
