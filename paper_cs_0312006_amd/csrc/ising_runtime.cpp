@@ -491,7 +491,8 @@ int ctx_prepare_plan(ising_ctx* ctx) {
     if (const uint32_t G = generic_bands(ctx)) {
         int rc = ctx_band_slots(ctx, band_slot_words(ctx->L, G));
         if (rc == ISING_OK) rc = ctx_band_part(ctx, G);  // here: ising_sweep_static may not allocate
-        if (rc != ISING_OK) return rc;
+        // without room for the bands the context runs its per-site launches
+        if (rc != ISING_OK && rc != ISING_ENOMEM) return rc;
     }
     uint32_t need = 0;
     const Planes pl = ctx_planes(ctx);
@@ -704,7 +705,7 @@ static int sweep_generic(ising_ctx* ctx, uint64_t n, int64_t* ser) {
     // 46 us for the call at 66^2; from two sweeps the bands win, 46 against 61).
     const bool direct = (n == 1 && ctx->L <= 256u) || stream_capturing(ctx->stream);
     const uint32_t G = direct ? 0 : generic_bands(ctx);
-    if (G && ctx->band_part_cap >= G)
+    if (G && ctx->band_part_cap >= G && ctx->band_words >= band_slot_words(ctx->L, G))
         return sweep_bands(ctx, n, ser, ctx->band_part, kBandChunk, band_default_rows(ctx->L), 1u);
     const uint32_t k0 = (uint32_t)ctx->p.seed, k1 = (uint32_t)(ctx->p.seed >> 32);
     HIP_TRY(ctx, launch_zero(ser, 2 * n, ctx->stream));

@@ -70,3 +70,26 @@ def test_large_read_backs_go_on_without_helpers(fail, cpus):
             h.fail_{fail} = -1
             assert rc == 0 and not out.any(), rc
     """)
+
+
+def test_a_per_site_context_needs_no_room_for_bands():
+    """Sides that are not multiples of 8 run on bands where there is memory
+    for their words and partial sums; without it the context is created all
+    the same and runs per-site launches."""
+    hip_host.run("""
+        for k in range(8):
+            h.fail_malloc = k  # the lattice, the observables' scratch, then the bands' memory
+            try:
+                c = b.ising_create(1002)
+            except b.IsingError as e:
+                assert e.code == b.ISING_ENOMEM and k < 2, (k, e.code)
+                continue
+            finally:
+                h.fail_malloc = -1
+            n, m = h.cooperative, h.launches
+            b.ising_sweep(c, 3)
+            assert h.cooperative - n == (1 if k >= 4 else 0), (k, h.cooperative - n)
+            assert k >= 4 or h.launches - m >= 9
+            b.ising_copy_spins(c, 1002)
+            b.ising_destroy(c)
+    """)
