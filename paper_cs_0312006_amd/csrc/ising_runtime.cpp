@@ -701,9 +701,10 @@ static int sweep_replays(ising_ctx* ctx, uint64_t n, uint64_t* left) {
 
 static int sweep_generic(ising_ctx* ctx, uint64_t n, int64_t* ser) {
     // not under capture: a band launch's tags advance on the host. One sweep
-    // of a small lattice is faster as its three per-site launches (38 against
-    // 46 us for the call at 66^2; from two sweeps the bands win, 46 against 61).
-    const bool direct = (n == 1 && ctx->L <= 256u) || stream_capturing(ctx->stream);
+    // of a small lattice is faster as its three per-site launches: call and wait
+    // 22.6 us against 30 at 66^2, 25.0 and 30.0 at 258^2, 28.9 and 30.2 at 386^2,
+    // 31.5 and 30.3 at 450^2; two sweeps are level at 66^2 (30.0 and 30.9).
+    const bool direct = (n == 1 && ctx->L <= 400u) || stream_capturing(ctx->stream);
     const uint32_t G = direct ? 0 : generic_bands(ctx);
     if (G && ctx->band_part_cap >= G && ctx->band_words >= band_slot_words(ctx->L, G))
         return sweep_bands(ctx, n, ser, ctx->band_part, kBandChunk, band_default_rows(ctx->L), 1u);

@@ -110,3 +110,15 @@ def test_read_backs_into_pinned_memory_are_one_copy(L):
                 assert read(c, dst, N) == 0
                 assert h.copies - n == copies, (h.copies - n, copies)
     """)
+
+
+@pytest.mark.parametrize("L,direct", [(66, True), (258, True), (398, True), (402, False), (1002, False)])
+def test_single_sweeps_of_small_partial_word_sides(L, direct):
+    """One sweep of such a side is faster as per-site launches up to 400."""
+    hip_host.run(f"""
+        c = b.ising_create({L})
+        b.ising_sweep(c, 1)
+        assert h.cooperative == {0 if direct else 1}
+        b.ising_sweep(c, 2)
+        assert h.cooperative == {1 if direct else 2}
+    """)
