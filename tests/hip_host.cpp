@@ -2,6 +2,7 @@
 // malloc, copies are memcpy, kernels are counted and not run. Loaded with
 // RTLD_GLOBAL before the library (tests/hip_host.py), so that tests without a
 // GPU can follow its host side, with failures injected.
+#include <atomic>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -23,7 +24,7 @@ long host_fail_malloc = -1;       // this many further device allocations succee
 long host_fail_set_device = -1;   // as above, hipSetDevice
 long host_fail_new = -1;          // as above, operator new
 long host_live = 0;               // bytes of device memory allocated
-long host_mallocs = 0, host_launches = 0, host_cooperative = 0, host_copies = 0;
+std::atomic<long> host_mallocs{0}, host_launches{0}, host_cooperative{0}, host_copies{0};
 long host_capturing = 0;           // every stream is being captured
 long host_mark = 0;                // cooperative launches set the 4-byte words of pinned memory (time-out marks)
 
