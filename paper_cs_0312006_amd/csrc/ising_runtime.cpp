@@ -213,12 +213,12 @@ static bool untuned_plan(uint32_t L, Plan* out) {
     if (L % 8u != 0u) return plan_for(L, ISING_PLAN_GENERIC, 0, 0, out);
     if (L <= kResidentMaxL) return plan_for(L, ISING_PLAN_RESIDENT, 0, 0, out);
     if (L >= kBandMinDefaultL && plan_for(L, ISING_PLAN_BANDS, 0, 0, out)) return true;
-    // Wave tiles before full rows, whose waves a barrier couples: us a sweep,
+    // Wave tiles, which serve every side that full-row workgroups do, rather than
+    // those, whose waves a barrier couples (ising_tune compares them): us a sweep,
     // tiles against rows, 18432^2 171 and 268, 24576^2 267 and 350, 28672^2 362
     // and 447, and where the rows' bands are whole rounds of one workgroup of 16
     // waves a compute unit, 32768^2, 466 and 475.
     if (plan_for(L, ISING_PLAN_FUSED, 0, 0, out)) return true;
-    if (plan_for(L, ISING_PLAN_FUSED_ROWS, 0, 0, out)) return true;
     return plan_for(L, ISING_PLAN_TWO_PASS, 0, 0, out);
 }
 
