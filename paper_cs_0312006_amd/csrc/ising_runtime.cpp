@@ -222,6 +222,11 @@ static bool untuned_plan(uint32_t L, Plan* out) {
     return plan_for(L, ISING_PLAN_TWO_PASS, 0, 0, out);
 }
 
+static bool tuned_side(uint32_t L) {
+    std::lock_guard<std::mutex> g(g_tuned_mu);
+    return g_tuned.find(L) != g_tuned.end();
+}
+
 static bool is_side_plan(uint32_t L, const Plan& p) {
     Plan d;
     return untuned_plan(L, &d) && d.kind == p.kind && d.cw == p.cw && d.rows == p.rows;
@@ -746,7 +751,7 @@ static int create_common(const ising_params* params, void* dev_buf, size_t bytes
     ctx->p = *params;
     ctx->L = params->L;
     ctx->plan = plan;
-    ctx->plan_by_side = (params->flags & 0xffu) == ISING_PLAN_AUTO && is_side_plan(params->L, plan);
+    ctx->plan_by_side = (params->flags & 0xffu) == ISING_PLAN_AUTO && (!tuned_side(params->L) || is_side_plan(params->L, plan));
     build_accept_table(params->J, params->h, params->T, &ctx->table, &ctx->exact);
     hostcopy_retain();
     if (hipGetDevice(&ctx->device) != hipSuccess) {
