@@ -59,10 +59,10 @@ PROFILED_CREUTZ = {"kernel": "k_creutz_pairs<4>",
 # sweeps) and the stepped plan's fused walk (profiles/k_multi_fused_batched_1024.md,
 # mean of 160 dispatches, 16-row tiles)
 BATCH_FILES = ("ising_batch.hip", "ising_bits.hpp", "ising_device.hpp", "ising_launch.hpp")
-PROFILED_BATCH_SOURCES = "3b566fa8596fe164"
+PROFILED_BATCH_SOURCES = "047fbbaab0662ebb"
 PROFILED_BATCH = {"kernel": "k_batch (bit-packed lattices in workgroup memory)",
                   "valu_lane_ops_per_attempt": 192747224258.0 * 64 / (388630784 * 2000),
-                  "valu_busy_rocprof": 0.934}
+                  "valu_busy_rocprof": 0.929}
 MULTI_FUSED_FILES = ("ising_multi_fused.hip", "ising_fused_core.hpp", "ising_device.hpp", "ising_launch.hpp")
 PROFILED_MULTI_FUSED_SOURCES = "d149c70c430dab77"
 PROFILED_MULTI_FUSED = {"kernel": "k_multi_fused (one launch per sweep)",

@@ -55,9 +55,10 @@
 // and written at the end, behind a flag with which each band says that its
 // reads are done.
 //
-// One MI355X, us a sweep: 64^2 1.6, 512^2 1.57 (167 site updates/ns),
-// 1024^2 2.03 (517), 1002^2 2.5, 2048^2 3.27 (1283), 4096^2 7.1 (2363); before
-// and after at each side: row_bands_serve. Up to 1024 the rest is latency
+// One MI355X, us a sweep over calls of 2048 and more: 64^2 to 512^2 1.39 (at
+// 512^2 189 site updates/ns), 1000^2 1.83, 1002^2 2.12, 1024^2 1.79 (586),
+// 2048^2 3.02 (1389), 3072^2 5.38, 4096^2 6.88 (2438), with and without a field;
+// before and after at each side: row_bands_serve. Up to 1024 the rest is latency
 // (an exchange of about 1 us per two sweeps, and per half-sweep two LDS round
 // trips, a barrier and one row's 45 to 90 dependent operations); at 4096 the
 // four waves of each SIMD keep the vector units busy.

@@ -247,10 +247,10 @@ uint32_t bands_capacity(uint32_t threads, uint32_t lds_bytes, bool general, uint
 // A wave per row wherever a row fits a wave's registers and a band its
 // workgroup (at most 16 waves): measured against the bands of a lattice kept
 // as bits, and against the byte bands with an exchange every half-sweep that
-// this replaced, us a sweep at the default band heights: 512 1.57 against
-// 3.11 (bytes), 1000 2.0 against 4.19 (bits) and, h != 0, 5.74, 1024 2.03
-// against 3.18 (bytes), 2048 3.27 against 4.82 (bytes), 3072 5.6 against 6.8
-// (bits), 4096 7.1 against 8.44 (bits) and, h != 0, 9.38 (bytes). Larger
+// this replaced, us a sweep at the default band heights: 512 1.39 against
+// 3.08 (bytes), 1000 1.83 against 4.15 (bits) and, h != 0, 5.69, 1024 1.79
+// against 3.14 (bytes), 2048 3.02 against 4.80 (bytes), 3072 5.38 against 6.69
+// (bits), 4096 6.88 against 8.40 (bits) and, h != 0, 9.35 (bytes). Larger
 // sides need more rows a band than a workgroup has waves, and stay bits.
 bool row_bands_serve(uint32_t L, uint32_t G, bool creutz) {
     RowBandShape sh;

@@ -135,8 +135,9 @@ __device__ __forceinline__ void run_lattice(const LdsTable& lt, const BatchItem&
 // bounds such a lattice is the latency of a half-sweep: a barrier, an LDS
 // read of three neighbour words, the table read, 45 operations a word. In bits most
 // threads would idle (64^2 holds 64 words a colour). Against the loop over
-// chunks below, us a sweep of one lattice: 64^2 0.50 against 1.40, 96^2 0.83
-// against 2.35, 128^2 1.16 against 3.69.
+// chunks below, us a sweep of one lattice: 16^2 0.50 against 1.11, 64^2 0.78
+// against 1.37, 88^2 1.10 against 2.08 (a word a thread), 96^2 1.88 against 2.37,
+// 128^2 1.88 against 3.64 (two), 176^2 3.50 against 5.49 (four).
 template <int K>
 __device__ __forceinline__ void run_small(const LdsTable& lt, const BatchItem& it, uint32_t* __restrict__ lat,
                                           uint32_t (*part)[kMaxWaves][2]) {

@@ -191,11 +191,11 @@ static bool bands_fit(uint32_t L, uint32_t rows, uint32_t per_wave) {
 
 // Default band height: about one band per compute unit, but at least four
 // rows (a band of four trades its edges every four half-sweeps, one of two
-// every two: 256^2 1.60 us a sweep with four rows, 1.95 with two, 2.56 with
-// one; 512^2 1.57 and 1.98; every band: 1002^2 takes five rows, not bands of
-// three and four), and 16 rows rather than 12 to 15 (no rows
-// outside the band to update: 3072^2 5.6 us with 16, 5.9 with 12; eight to
-// eleven rows measure the same as 16 or better).
+// every two: 256^2 1.40 us a sweep with four rows, 1.49 with two, 2.24 with
+// one; 512^2 1.39 and 1.45; every band: 1002^2 takes five rows, not bands of
+// three and four), and 16 rows rather than 12 to 15 (level, 3072^2 5.39 us with
+// 16 and 5.40 with 12, in fewer workgroups; eight to eleven rows measure the same
+// as 16 or better, 2816^2 5.59 with 11 and 5.64, 2048^2 3.01 with 8 and 3.87).
 static uint32_t band_default_rows(uint32_t L) {
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
@@ -438,7 +438,7 @@ static int ctx_band_part(ising_ctx* ctx, uint32_t G) {
 // multiple of 8: its sweeps run band-resident, a wave per row, where the
 // rows fit (0: they do not, or the plan was forced on a side of whole
 // words). A per-site sweep is three launches, one of them a whole pass for
-// the observables: 57.4 us at 1002^2 against 2.5 us.
+// the observables: 57.2 us at 1002^2 against 2.1 us.
 static uint32_t generic_bands(const ising_ctx* ctx) {
     if (ctx->plan.kind != ISING_PLAN_GENERIC || ctx->L % 8u == 0u) return 0;
     const uint32_t G = band_count(ctx->L, band_default_rows(ctx->L));
