@@ -370,7 +370,9 @@ int ising_creutz_init(ising_ctx* ctx, const uint8_t* host, size_t n, uint8_t fil
 /* Enqueue n Creutz sweeps (reverse != 0: n reversed sweeps) on the
  * context's stream and record (B, M) after each in the per-sweep series,
  * as ising_sweep does. Draws no random numbers and leaves the Metropolis
- * sweep index t unchanged. Asynchronous. Errors: EINVAL (NULL ctx), ESTATE
+ * sweep index t unchanged. Asynchronous. The context keeps what its sweeps
+ * take beside the demons: up to 4096 the edge words of the bands (3 MB at 512,
+ * 19 MB at 2048), beyond a second lattice and second demons (2 L*L bytes). Errors: EINVAL (NULL ctx), ESTATE
  * (no demons: call ising_creutz_init first; or poisoned), ENOMEM, EDEVICE. */
 int ising_creutz_sweep(ising_ctx* ctx, uint64_t n, int reverse);
 
