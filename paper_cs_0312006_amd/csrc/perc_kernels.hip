@@ -156,7 +156,7 @@ __global__ void __launch_bounds__(kThreads) k_perc_seed(const Medium* __restrict
     const uint32_t m = blockIdx.x;
     const Medium& md = media[m];
     auto add = [&](uint32_t tx, uint32_t ty) {
-        const uint32_t t = ty * md.n_tx + tx, p = list_part(tx, ty);
+        const uint32_t t = ty * md.n_tx + tx, p = list_part(m, tx, ty);
         md.queued[0][t] = 1u;
         w.list[0][(size_t)p * w.cap + atomicAdd(&w.len[p], 1u)] = make_uint2(m, t);
     };
@@ -307,7 +307,7 @@ __global__ void __launch_bounds__(kRelaxThreads) k_perc_relax(Medium one, const 
             if (want && nty >= 0 && nty < (int)n_ty && ntx >= 0 && ntx < (int)n_tx) {
                 const uint32_t t = (uint32_t)nty * n_tx + (uint32_t)ntx;
                 if (atomicExch(&q_out[t], 1u) == 0u) {
-                    const uint32_t p = list_part((uint32_t)ntx, (uint32_t)nty);
+                    const uint32_t p = list_part(m, (uint32_t)ntx, (uint32_t)nty);
                     const uint32_t pos = atomicAdd(&w.len[lout * kSubs + p], 1u);
                     list_out[(size_t)p * w.cap + pos] = make_uint2(m, t);
                 }
