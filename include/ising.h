@@ -231,8 +231,8 @@ int ising_load_spins(ising_ctx* ctx, const int8_t* host, size_t n, uint64_t t);
  * side is from 96 to 16384 (and fits the band-resident plan) runs on that
  * plan instead, on the context's stream ordered after `stream`'s earlier
  * work and before its later work (neither batch plan can spread one lattice
- * over the chip). Lattices may differ in L, J, h, T and seed;
- * each must satisfy L % 8 == 0 and have no pending device error. Contexts
+ * over the chip); EUNSUPPORTED if either stream is being captured. Lattices
+ * may differ in L, J, h, T and seed; each must satisfy L % 8 == 0 and have no pending device error. Contexts
  * are validated before anything is launched (all-or-nothing). The results
  * are bit-identical to calling ising_sweep on each context alone.
  * Asynchronous; the contexts' own streams are ordered after it. */

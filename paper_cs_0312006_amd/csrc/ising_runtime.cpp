@@ -1058,6 +1058,8 @@ int ising_sweep_batch(ising_ctx* const* ctxs, const uint64_t* n_sweeps, size_t c
 static int lone_band_batch(ising_ctx* ctx, uint64_t n, hipStream_t s) {
     int rc = ctx_enter(ctx);  // the engine orders this context afresh next time
     if (rc != ISING_OK) return rc;
+    // a replayed band launch would find its own edge words under the tags it waits for
+    if (stream_capturing(ctx->stream) || (s && stream_capturing(s))) return ISING_EUNSUPPORTED;
     Plan bp;
     if (!plan_for(ctx->L, ISING_PLAN_BANDS, 0, 0, &bp)) return ISING_EUNSUPPORTED;
     const uint32_t G = band_count(ctx->L, bp.rows);

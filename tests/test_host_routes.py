@@ -122,3 +122,25 @@ def test_single_sweeps_of_small_partial_word_sides(L, direct):
         b.ising_sweep(c, 2)
         assert h.cooperative == {1 if direct else 2}
     """)
+
+
+@pytest.mark.parametrize("L", [96, 184, 1024])
+def test_a_lone_batch_on_a_captured_stream_is_refused(L):
+    """Its band launches cannot be replayed: the edge words of one replay
+    carry the tags that the next one waits for."""
+    hip_host.run(f"""
+        c = b.ising_create({L})
+        b.ising_sweep_batch([c], [3])
+        assert h.cooperative == 1
+        h.capturing = 1
+        for stream in (None, 1):
+            try:
+                b.ising_sweep_batch([c], [3], stream=stream)
+            except b.IsingError as e:
+                assert e.code == b.ISING_EUNSUPPORTED
+            else:
+                raise AssertionError("captured")
+        h.capturing = 0
+        b.ising_sweep_batch([c], [3])
+        assert h.cooperative == 2 and b.ising_observables(c)[0].sweeps_done == 6
+    """)
