@@ -232,8 +232,9 @@ int ising_load_spins(ising_ctx* ctx, const int8_t* host, size_t n, uint64_t t);
  * plan instead, on the context's stream ordered after `stream`'s earlier
  * work and before its later work (neither batch plan can spread one lattice
  * over the chip); EUNSUPPORTED if either stream is being captured. Lattices
- * may differ in L, J, h, T and seed; each must satisfy L % 8 == 0 and have no pending device error. Contexts
- * are validated before anything is launched (all-or-nothing). The results
+ * may differ in L, J, h, T and seed; each must satisfy L % 8 == 0 and have no
+ * pending device error. Contexts are validated before anything is launched
+ * (all-or-nothing). The results
  * are bit-identical to calling ising_sweep on each context alone.
  * Asynchronous; the contexts' own streams are ordered after it. */
 int ising_sweep_batch(ising_ctx* const* ctxs, const uint64_t* n_sweeps, size_t count, void* stream);
@@ -372,8 +373,8 @@ int ising_creutz_init(ising_ctx* ctx, const uint8_t* host, size_t n, uint8_t fil
  * as ising_sweep does. Draws no random numbers and leaves the Metropolis
  * sweep index t unchanged. Asynchronous. The context keeps what its sweeps
  * take beside the demons: up to 4096 the edge words of the bands (3 MB at 512,
- * 19 MB at 2048), beyond a second lattice and second demons (2 L*L bytes). Errors: EINVAL (NULL ctx), ESTATE
- * (no demons: call ising_creutz_init first; or poisoned), ENOMEM, EDEVICE. */
+ * 19 MB at 2048), beyond a second lattice and second demons (2 L*L bytes).
+ * Errors: EINVAL (NULL ctx), ESTATE (no demons: call ising_creutz_init first; or poisoned), ENOMEM, EDEVICE. */
 int ising_creutz_sweep(ising_ctx* ctx, uint64_t n, int reverse);
 
 /* Demon total (units of 4J) into *out. Synchronises. Errors as above. */

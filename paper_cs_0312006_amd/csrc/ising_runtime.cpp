@@ -751,7 +751,8 @@ static int create_common(const ising_params* params, void* dev_buf, size_t bytes
     ctx->p = *params;
     ctx->L = params->L;
     ctx->plan = plan;
-    ctx->plan_by_side = (params->flags & 0xffu) == ISING_PLAN_AUTO && (!tuned_side(params->L) || is_side_plan(params->L, plan));
+    const bool automatic = (params->flags & 0xffu) == ISING_PLAN_AUTO;
+    ctx->plan_by_side = automatic && (!tuned_side(params->L) || is_side_plan(params->L, plan));
     build_accept_table(params->J, params->h, params->T, &ctx->table, &ctx->exact);
     hostcopy_retain();
     if (hipGetDevice(&ctx->device) != hipSuccess) {

@@ -31,7 +31,8 @@ struct ising_ctx {
     ising_params p{};
     uint32_t L = 0;
     ising::Plan plan{};
-    bool plan_by_side = false;  // the plan AUTO gives the side (not one the caller set, nor one that beat it when tuned)
+    // the plan AUTO gives the side (not one the caller set, nor one that beat it when tuned)
+    bool plan_by_side = false;
     ising::AcceptTable table{};
     bool exact = false;        // some threshold is 0: use the 64-bit compare
     int device = 0;
